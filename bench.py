@@ -63,7 +63,7 @@ def _code_tokens(src: str) -> str:
 def kernel_source_hash() -> str:
     """Hash of the kernel source's code (comments and layout ignored)."""
     h = hashlib.sha256()
-    for f in ("paper_2202_00441_amd/csrc/fewbit.hip",):
+    for f in ("paper_2202_00441_amd/csrc/fewbit.hip", "paper_2202_00441_amd/csrc/fwd16_out.h"):
         with open(os.path.join(ROOT, f), encoding="utf-8") as fh:
             h.update(_code_tokens(fh.read()).encode())
     return h.hexdigest()[:16]
@@ -76,7 +76,8 @@ def kernel_name(kind: str, dtype: str, bits: int, act: str, n: int, table_min: i
         return f"bwd32_kernel<f32,{bits}>" if dtype == "f32" else f"bwd_kernel<{dtype},{bits}>"
     if dtype == "f32":
         return f"fwd32_kernel<f32,{bits},{act}>"
-    k = "fwd16_kernel" if n >= table_min else "fwd16v_kernel"
+    table = "fwd16full_kernel" if dtype == "f16" else "fwd16_kernel"
+    k = table if n >= table_min else "fwd16v_kernel"
     return f"{k}<{dtype},{bits},{act}>"
 
 
@@ -112,12 +113,12 @@ def _kernel_key(name: str):
     m = re.search(r"persist_kernel<([0-9]), ?([0-9])>", name)
     if m:
         return f"ceiling_{ {'0': 'copy', '1': 'fwd', '2': 'bwd'}[m.group(1)]}<persistent>"
-    m = re.search(r"(fwd16v_kernel|fwd16_kernel|fwd32_kernel|bwd32_kernel|bwd_kernel)<([0-9, ]+)>", name)
+    m = re.search(r"(fwd16v_kernel|fwd16full_kernel|fwd16_kernel|fwd32_kernel|bwd32_kernel|bwd_kernel)<([0-9, ]+)>", name)
     if not m:
         base = name.replace("(anonymous namespace)::", "").replace("void ", "")
         return base.split("(")[0].strip() or name
     args = [int(a) for a in m.group(2).split(",")]
-    if m.group(1) in ("fwd16_kernel", "fwd16v_kernel"):
+    if m.group(1) in ("fwd16_kernel", "fwd16full_kernel", "fwd16v_kernel"):
         return f"{m.group(1)}<{DT_NAMES[args[0]]},{args[1]},{ACT_NAMES[args[2]]}>"
     if m.group(1) == "fwd32_kernel":
         return f"fwd32_kernel<f32,{args[0]},{ACT_NAMES[args[1]]}>"
@@ -583,8 +584,8 @@ def main():
     out["bwd"]["kernel"] = kernel_name("bwd", w.dtype, bits, w.act, n, 0)
     if args.fwd_kernel != "auto":
         out["fwd_kernel_forced"] = args.fwd_kernel
-    if fwd_kernel.startswith("fwd16_kernel"):
-        # the table forward runs one persistent workgroup per CU: its rate
+    if fwd_kernel.startswith("fwd16full_kernel"):
+        # the full-range table forward runs one persistent workgroup per CU: its rate
         # against what that launch shape streams for the same bytes
         out["fwd"]["frac_of_persistent_shape"] = round(
             bytes_pass / (fwd_avg * 1e-3) / 1e9 / ceil["fwd_persistent_shape"]["GB/s"], 4)
@@ -781,7 +782,7 @@ def all_configs(args) -> None:
             tm = forced_min(P, w, bits, args.fwd_kernel)
             fk = kernel_name("fwd", w.dtype, bits, w.act, w.n, tm)
             fwd_rec = kernel_record(fwd, b, w.n, ceil["fwd"])
-            if fk.startswith("fwd16_kernel"):
+            if fk.startswith("fwd16full_kernel"):
                 fwd_rec["frac_of_persistent_shape"] = round(
                     b / (sum(fwd) / len(fwd) * 1e-3) / 1e9 / ceil["fwd_persistent_shape"]["GB/s"], 4)
             print(json.dumps({

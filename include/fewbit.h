@@ -177,13 +177,16 @@ int64_t fewbit_packed_words(int64_t n, int32_t bits);
 int fewbit_fwd(const fewbit_table* t, int32_t dtype, const void* x, void* y,
                uint32_t* codes, int64_t n, void* stream);
 
-/* Which of the two fp16 / bf16 forward kernels fewbit_fwd runs: from the
- * returned element count on, the table kernel (outputs and interval indices
- * looked up per input bit pattern in tables each workgroup builds in LDS);
+/* Which kind of fp16 / bf16 forward kernel fewbit_fwd runs: from the
+ * returned element count on, a table kernel (outputs and interval indices
+ * looked up per input bit pattern in tables each workgroup puts in LDS);
  * below it, the per-element kernel (f and the compares evaluated for every
  * element).  The count depends on the activation, the bit width and the
  * type (dtype FEWBIT_F16 or FEWBIT_BF16); INT64_MAX where the per-element
- * kernel runs at every size.  Both kernels give results within the same
+ * kernel runs at every size.  bf16 forwards of 6 to 8 Mi elements use the
+ * table kernel at every bit width; the count is that of bf16 tables whose
+ * boundaries are 0 or of ordinary size (2^-9 to 15 in magnitude): others
+ * switch at larger sizes.  All kernels give results within the same
  * bounds: indices and codes identical, y within one unit in the last place
  * of the correctly rounded f.  This only tells a caller (or a test) which
  * kernel a given n reaches.  Returns -1 for an unknown activation, bits

@@ -22,6 +22,7 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-fno-gpu-flush-denormals-to-zero", "-fno-fast-math", "-ffp-contract=on",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-fconstexpr-steps=200000000",
     "-Wall", "-I", os.path.join(ROOT, "include"),
 ]
 

@@ -22,18 +22,18 @@
 // Streams are read and written with non-temporal 16-byte buffer accesses
 // (nothing is reused).  Most kernels run one wave per tile (the per-element
 // fp16 / bf16 forward one wave per two tiles) and let the hardware
-// dispatcher balance the compute units; the table-based fp16 / bf16 forward
-// is persistent (see the launch-shape knobs below).
+// dispatcher balance the compute units; the forward with full-range tables is
+// persistent (see the launch-shape knobs below).
 //
 // fp16 / bf16 forward.  Output pattern and interval index are functions of
-// the 16-bit input pattern alone, so from a size that depends on the type,
-// activation and bit width (kTableMinLog2) each workgroup looks both up in
-// LDS tables over all 65536 patterns, which it builds itself: the outputs
-// (mostly by rule, f where no rule holds) and the indices (4 bits per
-// pattern, from the boundaries).  A lookup costs two LDS reads instead of an
-// evaluation of f and the compares.  Smaller fp16 / bf16 forwards (and those
-// whose f and compares are cheap enough), and every fp32 forward, evaluate f
-// and search the boundaries per element.
+// the 16-bit input pattern alone.  bf16 (fwd16_kernel): the few thousand
+// patterns on which an activation is neither linear nor constant have one LDS
+// word each, from which output and index both follow.  fp16, and bf16 tables
+// whose boundaries that range does not hold (fwd16full_kernel): each workgroup
+// looks both up in LDS tables over all 65536 patterns, which it builds itself.
+// Forwards below a size that depends on type, activation and bit width
+// (tab_by_size, kTableMinLog2), and every fp32 forward, evaluate f and search
+// the boundaries per element.
 //
 // The fitted table travels as kernel arguments (scalar registers); the
 // backward spreads the values over the lanes of one register and reads
@@ -47,6 +47,7 @@
 #include <cstdlib>
 
 #include "../../include/fewbit.h"
+#include "fwd16_out.h"
 #include "fwd16_rules.h"
 
 // Launch-shape knobs (compile time): threads per workgroup, workgroups per
@@ -56,9 +57,9 @@
 // hardware dispatcher hands out workgroups as earlier ones finish.  The
 // dispatcher balances the load between compute units, whose streaming rates
 // differ by a few per cent from one to another; a persistent grid ends only
-// when its slowest unit has walked its share.  The fp16 / bf16 forward holds
-// 160 KiB of tables per workgroup (all of a CU's LDS), built at its start, so
-// it is persistent with one workgroup per CU.
+// when its slowest unit has walked its share.  The full-range table forward
+// holds 160 KiB of tables per workgroup (all of a CU's LDS), built at its
+// start, so it is persistent with one workgroup per CU.
 #ifndef FEWBIT_FWD16_THREADS
 #define FEWBIT_FWD16_THREADS 512
 #endif
@@ -691,7 +692,7 @@ __device__ inline WaveIndex wave_index() {
           static_cast<int64_t>(gridDim.x) * kPerBlock};
 }
 
-// ---------------------------------------------------------------- forward, fp16 / bf16
+// ---------------------------------------------------------------- forward, full-range tables
 // For 16-bit inputs both results of the forward are functions of the input
 // bit pattern alone, so every workgroup holds two tables over all 65536
 // patterns in LDS:
@@ -857,7 +858,7 @@ __device__ inline void fwd16_tile(u32x4_t in, const uint16_t* ylut, const uint8_
 }
 
 template <int DT, int BITS, int ACT>
-__global__ __launch_bounds__(FEWBIT_FWD16_THREADS) void fwd16_kernel(
+__global__ __launch_bounds__(FEWBIT_FWD16_THREADS) void fwd16full_kernel(
     const uint16_t* x, uint16_t* y, uint32_t* __restrict__ codes, int64_t n, int64_t nwords,
     TableArgs tab, int symmetric, OutRuns runs) {
   constexpr int U = FEWBIT_FWD16_UNROLL;
@@ -1013,6 +1014,197 @@ __global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
     }
     const int64_t wbase = t * kWords;
     pack_store<BITS>(Span(codes + wbase, kWords * 4), F, wi.lane, nwords - wbase);
+  }
+}
+
+// ---------------------------------------------------------------- forward, bf16, table
+// One LDS word per input pattern of the octaves that matter (fwd16_out.h):
+// the fp32 output factor, with the interval index in its low 4 bits.  An
+// element costs one ds_read_b32 and about eleven VALU operations at every
+// activation and bit width, the packing included, where evaluating f and the
+// compares takes up to thirty: bound by HBM.
+//
+// The table is 14-21 KiB, so 32 waves share a CU and the grid needs no
+// persistent walk: each wave takes kTabUnroll tiles, whose loads are in flight
+// while the table is put in place.  The factors are copied from constant
+// memory (they stay in the L2 caches: no HBM traffic), the indices are
+// searched for the patterns of each 16-byte chunk by the thread that copies
+// it; for most chunks the first and the last pattern's agree and the two
+// between need no search.
+//
+// Measured (GELU, 3 bits, back-to-back launches; the full-range table kernel,
+// the per-element kernel, this one): 2^23 elements 12.0, 9.9, 7.0 us; 12.6M
+// 14.8, 13.5, 11.5; 2^26 53.4, 57.0, 49.0; 2^28 202, 219, 186 (78.9% of
+// 8 TB/s; moving the same bytes with no work 182).  Two tiles per wave: one
+// leaves the table's cost on too few elements (2^28: 213 us in a probe), four
+// leave the last workgroups of a CU alone for longer (201).
+constexpr int kTabUnroll = 2;
+
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+
+// ReLU needs no factors: its words hold the index alone.
+template <int ACT>
+__device__ constexpr fwd16_out::Table<ACT> kOutTable = fwd16_out::make<ACT>();
+
+template <int ACT>
+struct OutForm {
+  static constexpr float kMax = fwd16_out::max_of(ACT);
+  // At |x| below 2^-126 GELU's and SiLU's x / 2 can be a tie: the index bits
+  // are cleared there so that the factor is exactly 1/2.
+  static constexpr bool kClear = ACT == FEWBIT_GELU || ACT == FEWBIT_SILU;
+  __device__ static float y(float x, uint32_t word) {
+    const float t = __uint_as_float(kClear ? word & ~15u : word);
+    if constexpr (ACT == FEWBIT_RELU) return Act<FEWBIT_BF16, FEWBIT_RELU>::f(x);
+    // maximum / minimum keep a NaN
+    if constexpr (ACT == FEWBIT_SOFTPLUS) return __builtin_elementwise_maximum(x, -0.0f) + t;
+    if constexpr (ACT == FEWBIT_SIGMOID)
+      return __builtin_elementwise_maximum(__builtin_elementwise_minimum(x, t), t);
+    if constexpr (ACT == FEWBIT_TANH)
+      return __builtin_elementwise_minimum(__builtin_elementwise_maximum(x, -kMax), kMax) * t;
+    return __builtin_elementwise_maximum(x, -kMax) * t;
+  }
+};
+
+// Byte offsets of the table words of the two patterns of w.
+template <int ACT>
+__device__ inline uint32_t word_offsets(uint32_t w) {
+  constexpr uint16_t kBase2 = 2 * fwd16_out::base_of(ACT);
+  constexpr uint16_t kCount = fwd16_out::count_of(ACT);
+  const u16x2_t p = __builtin_bit_cast(u16x2_t, w);
+  // the sign, with -0 on the side of +0 (a boundary may lie at 0); the empty
+  // register barrier keeps the packed form (else: two compares and selects)
+  u16x2_t neg = __builtin_elementwise_sub_sat(p, (u16x2_t){1, 1});
+  asm("" : "+v"(neg));
+  neg = neg >> static_cast<uint16_t>(15);
+  // twice the magnitude pattern, brought into the range
+  u16x2_t m = __builtin_elementwise_sub_sat(static_cast<u16x2_t>(p << static_cast<uint16_t>(1)), (u16x2_t){kBase2, kBase2});
+  m = __builtin_elementwise_min(m, (u16x2_t){2 * (kCount - 1), 2 * (kCount - 1)});
+  m = neg * (u16x2_t){2 * kCount, 2 * kCount} + m;
+  return __builtin_bit_cast(uint32_t, static_cast<u16x2_t>(m << static_cast<uint16_t>(1)));
+}
+
+__device__ inline uint32_t table_word(const uint32_t* table, uint32_t offset) {
+  return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(table) + offset);
+}
+
+// The tile's outputs and its lanes' code fields.  Each word is rotated into
+// the field by its index bits alone (alignbit), element 0 first.  A NaN has
+// the output NaN by the arithmetic but shares its word with the infinity of
+// its sign: its index is 0, set in a branch that is taken only where a wave
+// holds one.
+template <int BITS, int ACT>
+__device__ inline void tab_tile(u32x4_t in, const uint32_t* table, u32x4_t& out, uint32_t& F) {
+  using H = Half<FEWBIT_BF16>;
+  uint32_t f = 0;
+  u16x2_t top = {0, 0};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t w = in[k];
+    const uint32_t o = word_offsets<ACT>(w);
+    const uint32_t t0 = table_word(table, o & 0xFFFFu), t1 = table_word(table, o >> 16);
+    out[k] = H::pack(OutForm<ACT>::y(H::lo(w), t0), OutForm<ACT>::y(H::hi(w), t1));
+    f = __builtin_amdgcn_alignbit(t0, f, BITS);
+    f = __builtin_amdgcn_alignbit(t1, f, BITS);
+    top = __builtin_elementwise_max(top, static_cast<u16x2_t>(__builtin_bit_cast(u16x2_t, w) << static_cast<uint16_t>(1)));
+  }
+  F = f >> (32 - 8 * BITS);
+  constexpr uint16_t kInf2 = 2 * H::kSpecialFrom;
+  if (__builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(top, (u16x2_t){kInf2, kInf2})) != 0) {
+#pragma unroll
+    for (int j = 0; j < kPerLane; ++j)
+      if (((in[j / 2] >> (16 * (j & 1))) & 0x7FFFu) > H::kSpecialFrom) F &= ~(((1u << BITS) - 1u) << (BITS * j));
+  }
+}
+
+// Tile of place q in the work of workgroup b.  RUN 0: consecutive tiles.
+// Else runs of RUN tiles are dealt to 8 consecutive workgroups, which the
+// dispatcher hands to the 8 XCDs, so that the addresses in flight across the
+// chip stay close together.
+template <int TILES, int RUN>
+__device__ inline int64_t tab_tile_at(int64_t b, int q) {
+  if constexpr (RUN == 0)
+    return b * TILES + q;
+  else
+    return (b >> 3) * (8 * TILES) + (q / RUN) * (8 * RUN) + static_cast<int>(b & 7) * RUN + q % RUN;
+}
+
+template <int DT, int BITS, int ACT, int THREADS, int RUN>
+__global__ __launch_bounds__(THREADS, 8) void fwd16_kernel(
+    const uint16_t* x, uint16_t* y, uint32_t* __restrict__ codes, int64_t n, int64_t nwords,
+    TableArgs tab, int symmetric) {
+  static_assert(DT == FEWBIT_BF16, "fp16's octaves hold eight times as many patterns");
+  using H = Half<DT>;
+  constexpr int kWords = 16 * BITS;
+  constexpr int kWaves = THREADS / kWave, kTiles = kWaves * kTabUnroll;
+  constexpr uint32_t kBase = fwd16_out::base_of(ACT), kCount = fwd16_out::count_of(ACT);
+  constexpr uint32_t kChunks = 2 * kCount / 4;         // 16-byte chunks of the table
+  __shared__ __attribute__((aligned(16))) uint32_t table[2 * kCount];
+  const int lane = static_cast<int>(threadIdx.x & (kWave - 1));
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+  const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
+  const int64_t full = n / kTile;
+  if (tab_tile_at<kTiles, RUN>(blockIdx.x, 0) * kTile >= n) return;      // the whole workgroup
+
+  // tiles past the last full one load nothing and store nothing (a span of 0 bytes)
+  int64_t t[kTabUnroll];
+  u32x4_t in[kTabUnroll];
+#pragma unroll
+  for (int u = 0; u < kTabUnroll; ++u) {
+    t[u] = tab_tile_at<kTiles, RUN>(blockIdx.x, u * kWaves + wave);
+    in[u] = Span(x + t[u] * kTile, t[u] < full ? kSpanBytes : 0u).ld16(lane_b);
+  }
+
+  const Search<BITS> cl(tab, lane, symmetric);
+#pragma unroll
+  for (uint32_t c0 = 0; c0 < kChunks; c0 += THREADS) {
+    const uint32_t c = c0 + threadIdx.x;
+    if (c0 + THREADS > kChunks && c0 + wave * kWave >= kChunks) break;     // whole waves
+    u32x4_t w = {0u, 0u, 0u, 0u};
+    if constexpr (ACT != FEWBIT_RELU) w = reinterpret_cast<const u32x4_t*>(kOutTable<ACT>.e)[c];
+    const bool neg = 4u * c >= kCount;
+    const uint32_t p = kBase + 4u * c - (neg ? kCount : 0u) + (neg ? 0x8000u : 0u);
+    uint32_t i[4];
+    i[0] = cl.code(H::widen(p));
+    i[3] = cl.code(H::widen(p + 3u));
+    i[1] = i[2] = i[0];
+    if (__any(i[0] != i[3])) {        // by whole waves: the search reads other lanes
+      i[1] = cl.code(H::widen(p + 1u));
+      i[2] = cl.code(H::widen(p + 2u));
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] |= i[j];
+    reinterpret_cast<u32x4_t*>(table)[c] = w;
+  }
+  __syncthreads();
+
+#pragma unroll
+  for (int u = 0; u < kTabUnroll; ++u) {
+    u32x4_t out;
+    uint32_t F;
+    tab_tile<BITS, ACT>(in[u], table, out, F);
+    const bool here = t[u] < full;
+    Span(y + t[u] * kTile, here ? kSpanBytes : 0u).st16(lane_b, out);
+    pack_store_full<BITS>(Span(codes + t[u] * kWords, here ? kWords * 4 : 0u), F, lane);
+  }
+  // the partial tile at the end, if any, by the wave whose tile it is
+  if (n % kTile != 0) {
+#pragma unroll
+    for (int u = 0; u < kTabUnroll; ++u) {
+      if (t[u] != full) continue;
+      uint32_t F = 0;
+#pragma unroll
+      for (int j = 0; j < kPerLane; ++j) {
+        const int64_t e = full * kTile + lane * kPerLane + j;
+        if (e < n) {
+          const uint32_t p = x[e];
+          const uint32_t word = table_word(table, word_offsets<ACT>(p) & 0xFFFFu);
+          y[e] = static_cast<uint16_t>(H::pack(OutForm<ACT>::y(H::widen(p), word), 0.0f) & 0xFFFFu);
+          if ((p & 0x7FFFu) <= H::kSpecialFrom) F |= (word & ((1u << BITS) - 1u)) << (BITS * j);
+        }
+      }
+      const int64_t wbase = full * kWords;
+      pack_store<BITS>(Span(codes + wbase, kWords * 4), F, lane, nwords - wbase);
+    }
   }
 }
 
@@ -1438,7 +1630,8 @@ OutRuns out_runs() {
   return r;
 }
 
-// log2 of the element count from which an fp16 / bf16 forward runs the table
+// log2 of the element count from which an fp16 forward, or a bf16 one whose
+// boundaries the compact table does not hold, runs the full-range table
 // kernel, by [type: fp16, bf16][activation][bits - 1]; 63: never.  The table
 // kernel builds its tables in every workgroup (7-10 us of fixed cost for
 // bf16, 12-15 us for fp16, whose tables need f in far more blocks) and runs
@@ -1478,6 +1671,50 @@ int64_t table_min_of(int dt, int act, int bits) {
   return lg >= 63 ? INT64_MAX : int64_t{1} << lg;
 }
 
+// The same for the bf16 kernel with the compact table, wherever the table's
+// boundaries allow it (fwd16_out::holds): log2 of the element count from
+// which it is ahead, by [activation][bits - 1].  Its cost does not depend on
+// the activation or the bit width, the per-element kernel's does: with 3 and
+// 4 bits it is ahead from 2^22 elements on (GELU 3-bit 6.2 -> 4.8 us, Sigmoid
+// 3-bit, the closest, 5.8 -> 4.9; at 2^21 3.9 -> 4.3), with 1 and 2 bits the
+// per-element kernel streams as fast until sustained load slows it (GELU
+// 1-bit, 2^25: 24.6 and 25.6 us; 2^28: 181 and 176).  SELU's table is the
+// largest, ReLU's f the cheapest but its table needs no factors.
+constexpr uint8_t kTabMinLog2[FEWBIT_SOFTPLUS + 1][4] = {
+    {27, 27, 22, 22},   // gelu
+    {27, 27, 22, 22},   // silu
+    {27, 27, 22, 22},   // sigmoid
+    {27, 27, 22, 22},   // tanh
+    {26, 26, 22, 22},   // relu
+    {28, 28, 22, 22},   // selu
+    {28, 27, 22, 22},   // softplus
+};
+
+int64_t tab_min_of(int act, int bits) { return int64_t{1} << kTabMinLog2[act][bits - 1]; }
+
+// At 1 and 2 bits it is also ahead where its workgroups of 32 tiles about
+// fill the chip's 512 places once: 1-bit GELU at 6, 8 and 9 Mi elements 6.8,
+// 8.6, 9.6 us per element, 6.4, 7.0, 9.5 by the table.
+bool tab_by_size(int act, int bits, int64_t n) {
+  return n >= tab_min_of(act, bits) || (n >= int64_t{6} << 20 && n <= int64_t{8} << 20);
+}
+
+// Workgroups of 16 waves that take consecutive tiles below, of 8 waves that
+// share runs of 4 tiles with 7 others from here on: 12.6M elements 11.5 and
+// 12.9 us, 2^25 27.0 and 26.8, 2^28 191 and 186.
+constexpr int64_t kTabLargeFrom = int64_t{1} << 25;
+
+template <int DT, int BITS, int ACT, int THREADS, int RUN>
+void launch_tab(const Launch& L, int64_t nw, int sym) {
+  // elements of a workgroup, or of the 8 that share runs of tiles
+  constexpr int64_t kGroups = RUN ? 8 : 1, kSpan = kGroups * (THREADS / kWave) * kTabUnroll * kTile;
+  const dim3 grid(static_cast<unsigned>((L.n + kSpan - 1) / kSpan * kGroups));
+  (void)hipGetLastError();
+  hipLaunchKernelGGL((fwd16_kernel<DT, BITS, ACT, THREADS, RUN>), grid, dim3(THREADS), 0, L.s,
+                     static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes, L.n,
+                     nw, table_args(L.t), sym);
+}
+
 template <int DT, int BITS, int ACT>
 void launch_fwd(const Launch& L) {
   const int64_t nw = fewbit_packed_words(L.n, BITS);
@@ -1489,18 +1726,27 @@ void launch_fwd(const Launch& L) {
                        static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n,
                        nw, table_args(L.t), sym);
   } else {
+    const bool holds = DT == FEWBIT_BF16 && fwd16_out::holds(ACT, sym != 0, L.t->s, (1 << BITS) - 1);
+    const bool by_size = holds ? tab_by_size(ACT, BITS, L.n) : L.n >= table_min_of(DT, ACT, BITS);
     const bool table = (L.t->flags & FEWBIT_FLAG_TABLE_FWD) ||
-                       (!(L.t->flags & FEWBIT_FLAG_ELEMENT_FWD) && L.n >= table_min_of(DT, ACT, BITS));
+                       (!(L.t->flags & FEWBIT_FLAG_ELEMENT_FWD) && by_size);
     if (!table) {
       const dim3 grid = grid_for(L.n, FEWBIT_FWD16V_THREADS / kWave, 0, FEWBIT_FWD16V_UNROLL);
       (void)hipGetLastError();
       hipLaunchKernelGGL((fwd16v_kernel<DT, BITS, ACT>), grid, dim3(FEWBIT_FWD16V_THREADS), 0, L.s,
                          static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes,
                          L.n, nw, table_args(L.t), sym);
+    } else if (holds) {
+      if constexpr (DT == FEWBIT_BF16) {
+        if (L.n < kTabLargeFrom)
+          launch_tab<DT, BITS, ACT, 1024, 0>(L, nw, sym);
+        else
+          launch_tab<DT, BITS, ACT, 512, 4>(L, nw, sym);
+      }
     } else {
       const dim3 grid = grid_for(L.n, FEWBIT_FWD16_THREADS / kWave, FEWBIT_FWD16_WG_PER_CU, FEWBIT_FWD16_UNROLL);
       (void)hipGetLastError();
-      hipLaunchKernelGGL((fwd16_kernel<DT, BITS, ACT>), grid, dim3(FEWBIT_FWD16_THREADS), 0, L.s,
+      hipLaunchKernelGGL((fwd16full_kernel<DT, BITS, ACT>), grid, dim3(FEWBIT_FWD16_THREADS), 0, L.s,
                          static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes,
                          L.n, nw, table_args(L.t), sym, out_runs<DT, ACT>());
     }
@@ -1600,7 +1846,7 @@ extern "C" int64_t fewbit_fwd16_table_min(int32_t act, int32_t bits, int32_t dty
   if (act < FEWBIT_GELU || act > FEWBIT_SOFTPLUS || bits < 1 || bits > 4 ||
       (dtype != FEWBIT_F16 && dtype != FEWBIT_BF16))
     return -1;
-  return table_min_of(dtype, act, bits);
+  return dtype == FEWBIT_BF16 ? tab_min_of(act, bits) : table_min_of(dtype, act, bits);
 }
 
 extern "C" int fewbit_bwd(const fewbit_table* t, int32_t dtype, const void* grad_out,

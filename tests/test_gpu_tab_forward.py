@@ -1,0 +1,74 @@
+"""The bf16 table forward at the sizes where its tiling can go wrong, and with
+boundaries at the edges of what its table holds, against the oracle: codes
+and grad_in bit-exact, y within one unit in the last place.  Sizes: one
+element, both sides of a tile and of a workgroup's 32 tiles (or 8
+workgroups' 16), and both sides of the size where the launch shape changes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2202_00441_amd as P
+from parity import OACT, THREADS, check_exact, check_y, download, download_codes, upload
+
+pytestmark = pytest.mark.gpu
+
+WG = 32 * 512
+LARGE = 1 << 25
+SIZES = [1, 511, 512, 513, WG - 1, WG, WG + 513, 9 * WG + 7,
+         LARGE - 1, LARGE, LARGE + 65536 + 1, LARGE + 3 * 512 + 5]
+
+
+def _check(act, bits, s, v, x_bits, symmetric=False, label=""):
+    n = x_bits.size
+    flags = P.FLAG_TABLE_FWD | (P.FLAG_SYMMETRIC if symmetric else 0)
+    table = P.Table.from_values(P.ACTS[act], bits, s, v, flags=flags)
+    print(f"[tab] {act} b{bits} n={n} sym={symmetric} {label}", flush=True)
+    guard = 64
+    x = upload(x_bits, "bf16")
+    y = torch.full((n + guard,), -7.0, dtype=torch.bfloat16, device="cuda")
+    words = P.packed_words(n, bits)
+    codes = torch.full((words + guard,), -7, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    assert P.fwd_raw(table, P.BF16, x.data_ptr(), y.data_ptr(), codes.data_ptr(), n, stream) == 0
+    torch.cuda.synchronize()
+    assert (y[n:] == -7.0).all() and (codes[words:] == -7).all(), "written past the end"
+    y_ref, c_ref = O.fwd(OACT[act], O.BF16, bits, np.float32(s), x_bits, symmetric=symmetric, threads=THREADS)
+    check_exact(download_codes(codes[:words]), c_ref, f"{label} codes")
+    check_y(download(y[:n], "bf16"), y_ref, "bf16", f"{label} y")
+
+
+def _levels(bits):
+    k = 1 << bits
+    return [(-2.4 + 4.8 * (m + 1) / k) for m in range(k - 1)], [0.1 * m for m in range(k)]
+
+
+# the large shape by two activations, the smaller sizes by four
+CASES = [(a, b, n) for a, b in (("gelu", 3), ("selu", 2), ("tanh", 4), ("softplus", 1)) for n in SIZES
+         if n < LARGE - 1 or a in ("gelu", "selu")]
+
+
+@pytest.mark.parametrize("act,bits,n", CASES)
+def test_sizes(act, bits, n):
+    s, v = _levels(bits)
+    rng = np.random.default_rng(n % 1000003)
+    x = (rng.standard_normal(n, dtype=np.float32) * 3).view(np.uint32)
+    bits16 = (x >> 16).astype(np.uint16)
+    if n > 600:                                  # NaNs of both signs and infinities, wherever a wave may hold them
+        at = rng.integers(0, n, 40)
+        bits16[at] = np.resize(np.array([0x7FC1, 0xFFC1, 0x7F80, 0xFF80, 0x7F81, 0x8000], np.uint16), 40)
+    _check(act, bits, s, v, bits16, label=f"n={n}")
+
+
+@pytest.mark.parametrize("act", ["gelu", "silu", "sigmoid", "tanh", "relu", "selu", "softplus"])
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_boundaries_at_the_edges(act, symmetric):
+    # held by the table (0, ordinary sizes) and not held (tiny, huge): either
+    # way every pattern's code is the oracle's
+    pats = np.random.default_rng(3).permutation(np.arange(1 << 16, dtype=np.uint32).astype(np.uint16))
+    tiny, huge = 1e-39, 3e38
+    sets = [[0.0], [-0.0], [tiny], [-tiny], [huge], [-huge], [1e-3], [-1e-3], [15.0], [-15.0], [15.9375], [127.5],
+            [0.001953125], [-0.001953125]]
+    for s in sets:
+        _check(act, 1, s, [0.25, 0.75], pats, symmetric, label=f"s={s}")
+    _check(act, 2, [-1.5, 0.0, 1.5], [0.0, 0.25, 0.5, 1.0], pats, symmetric, label="around 0")
