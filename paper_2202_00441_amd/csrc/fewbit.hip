@@ -83,20 +83,11 @@
 #ifndef FEWBIT_FWD32_WG_PER_CU
 #define FEWBIT_FWD32_WG_PER_CU 0
 #endif
-#ifndef FEWBIT_FWD32_UNROLL
-#define FEWBIT_FWD32_UNROLL 1
-#endif
 #ifndef FEWBIT_BWD32_THREADS
 #define FEWBIT_BWD32_THREADS 256
 #endif
 #ifndef FEWBIT_BWD32_UNROLL
 #define FEWBIT_BWD32_UNROLL 1
-#endif
-#ifndef FEWBIT_NT_LOADS
-#define FEWBIT_NT_LOADS 1             // non-temporal stream loads
-#endif
-#ifndef FEWBIT_NT_STORES
-#define FEWBIT_NT_STORES 1            // non-temporal stream stores
 #endif
 
 namespace {
@@ -123,26 +114,32 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // every instruction (the non-temporal hint of plain loads and stores can be
 // dropped by the compiler when it merges or moves them), and the hardware
 // range check turns any access at or past `bytes` into a zero load or a
-// dropped store.  Cache-policy bits: 2 = nt (streaming, not kept in cache).
-constexpr int kLoadPolicy = FEWBIT_NT_LOADS ? 2 : 0;
-constexpr int kStorePolicy = FEWBIT_NT_STORES ? 2 : 0;
+// dropped store.
+//
+// Cache-policy bits: 2 = nt (streaming, not kept in cache), 16 = sc1 (device
+// scope: a store is written through the L2).  Loads are nt.  Stores are nt
+// alone, or through, or both, by the size of the tensor (store_nt).
+constexpr int kNt = 2, kThrough = 16, kThroughNt = 18;
 
 struct Span {
   __amdgpu_buffer_rsrc_t r;
   // 0x00020000: raw (unformatted) 32-bit buffer accesses on gfx9
   __device__ Span(const void* base, uint32_t bytes)
       : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(bytes), 0x00020000)) {}
-  __device__ u32x4_t ld16(uint32_t off) const {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kLoadPolicy);
-  }
-  __device__ void st16(uint32_t off, u32x4_t v) const {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kStorePolicy);
-  }
-  __device__ uint32_t ld4(uint32_t off) const {
-    return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kLoadPolicy);
-  }
+  __device__ u32x4_t ld16(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kNt); }
+  __device__ uint32_t ld4(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kNt); }
+};
+
+// A span that is stored to with the cache policy P.  Code words are never
+// kThroughNt: they are what the backward reads, and plain write-through leaves
+// them in the memory-side cache while there is room.  (A policy chosen at run
+// time, one scalar branch a store, cost every small launch 0.2 us.)
+template <int P>
+struct OutSpan : Span {
+  using Span::Span;
+  __device__ void st16(uint32_t off, u32x4_t v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, P); }
   __device__ void st4(uint32_t off, uint32_t v) const {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, kStorePolicy);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, P == kThroughNt ? kThrough : P);
   }
 };
 
@@ -579,7 +576,8 @@ __device__ inline uint32_t quad_read(uint32_t v) {
 }
 
 // word i of a code span
-__device__ inline void st_word(const Span& c, int i, uint32_t v) { c.st4(static_cast<uint32_t>(i) * 4u, v); }
+template <int P>
+__device__ inline void st_word(const OutSpan<P>& c, int i, uint32_t v) { c.st4(static_cast<uint32_t>(i) * 4u, v); }
 __device__ inline uint32_t ld_word(const Span& c, int i) { return c.ld4(static_cast<uint32_t>(i) * 4u); }
 
 // Lane field F holds the 8 codes of the lane (8*BITS bits, code j at bit
@@ -587,8 +585,8 @@ __device__ inline uint32_t ld_word(const Span& c, int i) { return c.ld4(static_c
 // field starts at stream bit 8*BITS*l.  Writes the words of the tile whose
 // index is below `valid` (the rest belong past the end of the buffer).
 // Must be called by all 64 lanes together.
-template <int BITS>
-__device__ inline void pack_store(const Span& out, uint32_t F, int lane, int64_t valid) {
+template <int BITS, int P>
+__device__ inline void pack_store(const OutSpan<P>& out, uint32_t F, int lane, int64_t valid) {
   if constexpr (BITS == 4) {
     if (lane < valid) st_word(out, lane, F);
   } else if constexpr (BITS == 2) {
@@ -640,8 +638,8 @@ __device__ inline uint32_t load_field(const Span& base, int lane, int64_t valid)
 // packing, a lane without a word of its own stores an identical copy of a
 // neighbour's word to the same address; when unpacking, lane 3 of each quad
 // reloads word 2 of the quad, which the permutes never read.
-template <int BITS>
-__device__ inline void pack_store_full(const Span& out, uint32_t F, int lane) {
+template <int BITS, int P>
+__device__ inline void pack_store_full(const OutSpan<P>& out, uint32_t F, int lane) {
   if constexpr (BITS == 4) {
     st_word(out, lane, F);
   } else if constexpr (BITS == 2) {
@@ -898,16 +896,16 @@ __global__ __launch_bounds__(FEWBIT_FWD16_THREADS) void fwd16full_kernel(
     for (int u = 0; u < U; ++u) fwd16_tile<BITS>(in[u], ylut, clut, out[u], F[u]);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      Span(y + (t0 + u) * kTile, kSpanBytes).st16(lane_b, out[u]);
-      pack_store_full<BITS>(Span(codes + (t0 + u) * kWords, kWords * 4), F[u], wi.lane);
+      OutSpan<kThroughNt>(y + (t0 + u) * kTile, kSpanBytes).st16(lane_b, out[u]);
+      pack_store_full<BITS>(OutSpan<kThroughNt>(codes + (t0 + u) * kWords, kWords * 4), F[u], wi.lane);
     }
   }
   for (int64_t t = groups * U + wi.wave; t < full; t += wi.nwaves) {
     u32x4_t out;
     uint32_t F;
     fwd16_tile<BITS>(Span(x + t * kTile, kSpanBytes).ld16(lane_b), ylut, clut, out, F);
-    Span(y + t * kTile, kSpanBytes).st16(lane_b, out);
-    pack_store_full<BITS>(Span(codes + t * kWords, kWords * 4), F, wi.lane);
+    OutSpan<kThroughNt>(y + t * kTile, kSpanBytes).st16(lane_b, out);
+    pack_store_full<BITS>(OutSpan<kThroughNt>(codes + t * kWords, kWords * 4), F, wi.lane);
   }
   // the partial tile at the end, if any, goes to the wave that would own it
   if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
@@ -923,7 +921,7 @@ __global__ __launch_bounds__(FEWBIT_FWD16_THREADS) void fwd16full_kernel(
       }
     }
     const int64_t wbase = t * kWords;
-    pack_store<BITS>(Span(codes + wbase, kWords * 4), F, wi.lane, nwords - wbase);
+    pack_store<BITS>(OutSpan<kThroughNt>(codes + wbase, kWords * 4), F, wi.lane, nwords - wbase);
   }
 }
 
@@ -955,7 +953,7 @@ __device__ inline void fwd16v_tile(u32x4_t in, const Search<BITS>& cl, u32x4_t& 
   }
 }
 
-template <int DT, int BITS, int ACT, bool SYM>
+template <int DT, int BITS, int ACT, bool SYM, int P>
 __device__ inline void fwd16v_tiles(const uint16_t* x, uint16_t* y, uint32_t* codes, int64_t full,
                                     const WaveIndex& wi, const Search<BITS>& cl) {
   constexpr int U = FEWBIT_FWD16V_UNROLL;
@@ -972,20 +970,20 @@ __device__ inline void fwd16v_tiles(const uint16_t* x, uint16_t* y, uint32_t* co
       u32x4_t out;
       uint32_t F;
       fwd16v_tile<DT, BITS, ACT, SYM>(in[u], cl, out, F);
-      Span(y + (t0 + u) * kTile, kSpanBytes).st16(lane_b, out);
-      pack_store_full<BITS>(Span(codes + (t0 + u) * kWords, kWords * 4), F, wi.lane);
+      OutSpan<P>(y + (t0 + u) * kTile, kSpanBytes).st16(lane_b, out);
+      pack_store_full<BITS>(OutSpan<P>(codes + (t0 + u) * kWords, kWords * 4), F, wi.lane);
     }
   }
   for (int64_t t = groups * U + wi.wave; t < full; t += wi.nwaves) {
     u32x4_t out;
     uint32_t F;
     fwd16v_tile<DT, BITS, ACT, SYM>(Span(x + t * kTile, kSpanBytes).ld16(lane_b), cl, out, F);
-    Span(y + t * kTile, kSpanBytes).st16(lane_b, out);
-    pack_store_full<BITS>(Span(codes + t * kWords, kWords * 4), F, wi.lane);
+    OutSpan<P>(y + t * kTile, kSpanBytes).st16(lane_b, out);
+    pack_store_full<BITS>(OutSpan<P>(codes + t * kWords, kWords * 4), F, wi.lane);
   }
 }
 
-template <int DT, int BITS, int ACT>
+template <int DT, int BITS, int ACT, int P>
 __global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
     const uint16_t* x, uint16_t* y, uint32_t* __restrict__ codes, int64_t n, int64_t nwords,
     TableArgs tab, int symmetric) {
@@ -995,9 +993,9 @@ __global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
   const int64_t full = n / kTile;
   const int64_t lane_off = static_cast<int64_t>(wi.lane) * kPerLane;
   if (symmetric)
-    fwd16v_tiles<DT, BITS, ACT, true>(x, y, codes, full, wi, cl);
+    fwd16v_tiles<DT, BITS, ACT, true, P>(x, y, codes, full, wi, cl);
   else
-    fwd16v_tiles<DT, BITS, ACT, false>(x, y, codes, full, wi, cl);
+    fwd16v_tiles<DT, BITS, ACT, false, P>(x, y, codes, full, wi, cl);
   // the partial tile at the end, if any, goes to the wave that would own it
   if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
     const int64_t t = full;
@@ -1013,7 +1011,7 @@ __global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
       }
     }
     const int64_t wbase = t * kWords;
-    pack_store<BITS>(Span(codes + wbase, kWords * 4), F, wi.lane, nwords - wbase);
+    pack_store<BITS>(OutSpan<P>(codes + wbase, kWords * 4), F, wi.lane, nwords - wbase);
   }
 }
 
@@ -1183,8 +1181,8 @@ __global__ __launch_bounds__(THREADS, 8) void fwd16_kernel(
     uint32_t F;
     tab_tile<BITS, ACT>(in[u], table, out, F);
     const bool here = t[u] < full;
-    Span(y + t[u] * kTile, here ? kSpanBytes : 0u).st16(lane_b, out);
-    pack_store_full<BITS>(Span(codes + t[u] * kWords, here ? kWords * 4 : 0u), F, lane);
+    OutSpan<kThroughNt>(y + t[u] * kTile, here ? kSpanBytes : 0u).st16(lane_b, out);
+    pack_store_full<BITS>(OutSpan<kThroughNt>(codes + t[u] * kWords, here ? kWords * 4 : 0u), F, lane);
   }
   // the partial tile at the end, if any, by the wave whose tile it is
   if (n % kTile != 0) {
@@ -1203,7 +1201,7 @@ __global__ __launch_bounds__(THREADS, 8) void fwd16_kernel(
         }
       }
       const int64_t wbase = full * kWords;
-      pack_store<BITS>(Span(codes + wbase, kWords * 4), F, lane, nwords - wbase);
+      pack_store<BITS>(OutSpan<kThroughNt>(codes + wbase, kWords * 4), F, lane, nwords - wbase);
     }
   }
 }
@@ -1231,8 +1229,8 @@ struct Codes32 {
 // of the lanes it covers (cross-lane reads of f0 | f1 << 16), and stores it;
 // lanes past 16*BITS store identical copies.  FULL: the whole tile exists,
 // so no store is masked off; else only words below `valid` are stored.
-template <int BITS, bool FULL>
-__device__ inline void pack_store32(const Span& out, uint32_t f0, uint32_t f1, int lane,
+template <int BITS, bool FULL, int P>
+__device__ inline void pack_store32(const OutSpan<P>& out, uint32_t f0, uint32_t f1, int lane,
                                     int64_t valid) {
   using C = Codes32<BITS>;
   const uint32_t both = f0 | (f1 << 16);
@@ -1276,47 +1274,27 @@ __device__ inline void fwd32_half(u32x4_t in, const Search<BITS>& cl, u32x4_t& o
   }
 }
 
-template <int BITS, int ACT>
+template <int BITS, int ACT, int P>
 __global__ __launch_bounds__(FEWBIT_FWD32_THREADS) void fwd32_kernel(
     const float* x, float* y, uint32_t* __restrict__ codes, int64_t n, int64_t nwords,
     TableArgs tab, int symmetric) {
-  constexpr int U = FEWBIT_FWD32_UNROLL;
   constexpr int kWords = Codes32<BITS>::kWords;
   const WaveIndex wi = wave_index<FEWBIT_FWD32_THREADS>();
   const Search<BITS> cl(tab, wi.lane, symmetric);
   const int64_t full = n / kTile;
-  const int64_t groups = full / U;
   const int64_t lane_off = static_cast<int64_t>(wi.lane) * 4;
   const uint32_t lane_b = static_cast<uint32_t>(wi.lane) * kLaneBytes;
 
-  for (int64_t gi = wi.wave; gi < groups; gi += wi.nwaves) {
-    const int64_t t0 = gi * U;
-    u32x4_t in[U][2], out[U][2];
-    uint32_t f[U][2];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) in[u][h] = Span(x + (t0 + u) * kTile + h * 256, kSpanBytes).ld16(lane_b);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) fwd32_half<BITS, ACT>(in[u][h], cl, out[u][h], f[u][h]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) Span(y + (t0 + u) * kTile + h * 256, kSpanBytes).st16(lane_b, out[u][h]);
-      pack_store32<BITS, true>(Span(codes + (t0 + u) * kWords, kWords * 4), f[u][0], f[u][1], wi.lane, kWords);
-    }
-  }
-  for (int64_t t = groups * U + wi.wave; t < full; t += wi.nwaves) {
-    u32x4_t out[2];
+  for (int64_t t = wi.wave; t < full; t += wi.nwaves) {
+    u32x4_t in[2], out[2];
     uint32_t f[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      fwd32_half<BITS, ACT>(Span(x + t * kTile + h * 256, kSpanBytes).ld16(lane_b), cl, out[h], f[h]);
-      Span(y + t * kTile + h * 256, kSpanBytes).st16(lane_b, out[h]);
-    }
-    pack_store32<BITS, true>(Span(codes + t * kWords, kWords * 4), f[0], f[1], wi.lane, kWords);
+    for (int h = 0; h < 2; ++h) in[h] = Span(x + t * kTile + h * 256, kSpanBytes).ld16(lane_b);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) fwd32_half<BITS, ACT>(in[h], cl, out[h], f[h]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) OutSpan<P>(y + t * kTile + h * 256, kSpanBytes).st16(lane_b, out[h]);
+    pack_store32<BITS, true>(OutSpan<P>(codes + t * kWords, kWords * 4), f[0], f[1], wi.lane, kWords);
   }
   // the partial tile at the end, if any, goes to the wave that would own it
   if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
@@ -1335,7 +1313,7 @@ __global__ __launch_bounds__(FEWBIT_FWD32_THREADS) void fwd32_kernel(
         }
       }
     const int64_t wbase = t * kWords;
-    pack_store32<BITS, false>(Span(codes + wbase, kWords * 4), f[0], f[1], wi.lane, nwords - wbase);
+    pack_store32<BITS, false>(OutSpan<P>(codes + wbase, kWords * 4), f[0], f[1], wi.lane, nwords - wbase);
   }
 }
 
@@ -1420,7 +1398,7 @@ struct BwdOrder {
   }
 };
 
-template <int DT, int BITS>
+template <int DT, int BITS, int P>
 __device__ inline void bwd16_full_tile(const uint16_t* g, const uint32_t* codes, uint16_t* gin,
                                        int64_t t, int lane, const TableArgs& tab) {
   constexpr int kWords = 16 * BITS;
@@ -1430,10 +1408,10 @@ __device__ inline void bwd16_full_tile(const uint16_t* g, const uint32_t* codes,
   // the stream loads are in flight before the values are put in place
   __builtin_amdgcn_sched_barrier(0);
   const Values<BITS> val(tab);
-  Span(gin + t * kTile, kSpanBytes).st16(lane_b, grad16_tile<DT, BITS>(in, F, val));
+  OutSpan<P>(gin + t * kTile, kSpanBytes).st16(lane_b, grad16_tile<DT, BITS>(in, F, val));
 }
 
-template <int DT, int BITS>
+template <int DT, int BITS, int P>
 __global__ __launch_bounds__(kWave) void bwd_kernel(
     const uint16_t* g, const uint32_t* __restrict__ codes, uint16_t* gin, int64_t n,
     int64_t nwords, TableArgs tab) {
@@ -1447,7 +1425,7 @@ __global__ __launch_bounds__(kWave) void bwd_kernel(
   // one unit per wave unless the grid was capped (see grid_for)
   for (int64_t u = wi.wave; u < units; u += wi.nwaves) {
     const int64_t t = BwdOrder<BITS>::tile_of_unit(u);
-    if (t < full) bwd16_full_tile<DT, BITS>(g, codes, gin, t, wi.lane, tab);
+    if (t < full) bwd16_full_tile<DT, BITS, P>(g, codes, gin, t, wi.lane, tab);
   }
   // the partial tile at the end, if any, goes to the wave of its unit
   if (n % kTile != 0 && wi.wave == BwdOrder<BITS>::unit_of_tile(full) % wi.nwaves) {
@@ -1478,7 +1456,7 @@ __device__ inline u32x4_t grad32_half(u32x4_t g, uint32_t f, const Values<BITS>&
   return out;
 }
 
-template <int BITS>
+template <int BITS, int P>
 __global__ __launch_bounds__(FEWBIT_BWD32_THREADS) void bwd32_kernel(
     const float* g, const uint32_t* __restrict__ codes, float* gin, int64_t n, int64_t nwords,
     TableArgs tab) {
@@ -1507,14 +1485,14 @@ __global__ __launch_bounds__(FEWBIT_BWD32_THREADS) void bwd32_kernel(
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        Span(gin + (t0 + u) * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in[u][h], f[u][h], val));
+        OutSpan<P>(gin + (t0 + u) * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in[u][h], f[u][h], val));
   }
   for (int64_t t = groups * U + wi.wave; t < full; t += wi.nwaves) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const u32x4_t in = Span(g + t * kTile + h * 256, kSpanBytes).ld16(lane_b);
       const uint32_t f = load_field32<BITS, true>(Span(codes + t * kWords, kWords * 4), h, wi.lane, kWords);
-      Span(gin + t * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in, f, val));
+      OutSpan<P>(gin + t * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in, f, val));
     }
   }
   if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
@@ -1610,6 +1588,20 @@ int check_stream_device(hipStream_t stream) {
     return FEWBIT_E_HIP;
   return owner == current ? FEWBIT_OK : FEWBIT_E_INVALID;
 }
+
+// Whether a launch that writes `bytes` of y or grad_in stores with nt alone.
+// Its lines then stay dirty in the 32 MB of L2 and are written back when the
+// kernel ends, with nothing left to overlap with: writing through is faster on
+// small tensors (a graph of 12 bf16 GELU layers of 2^17 elements, 24 kernels:
+// 63.5 -> 56.7 us) and on large ones (16-bit backward of 2^28 elements, 3
+// bits: 181.4 -> 175.5 us; fp16 SiLU 2-bit pass of 51.4M: 71.1 -> 67.1; fp32
+// Tanh 3-bit pass of 2^25: 90.4 -> 84.4).  From 1 MiB up to 16, where a stack of
+// layers fits the 256 MB memory-side cache but not the L2, nt alone is (12 fp16
+// SiLU layers of 2^20: 69.8 and 73.7 us).  y is stored nt as well as through
+// (its forward with through alone: 71.3 and 88.5 us on the two passes above),
+// the gradient is not (175.5 and 175.7, and 4.97 against 5.08 at 2^22).
+constexpr int64_t kNtFrom = int64_t{1} << 20, kNtUpto = int64_t{1} << 24;
+bool store_nt(int64_t bytes) { return bytes >= kNtFrom && bytes < kNtUpto; }
 
 struct Launch {
   const fewbit_table* t;
@@ -1720,9 +1712,10 @@ void launch_fwd(const Launch& L) {
   const int64_t nw = fewbit_packed_words(L.n, BITS);
   const int sym = (L.t->flags & FEWBIT_FLAG_SYMMETRIC) ? 1 : 0;
   if constexpr (DT == FEWBIT_F32) {
-    const dim3 grid = grid_for(L.n, FEWBIT_FWD32_THREADS / kWave, FEWBIT_FWD32_WG_PER_CU, FEWBIT_FWD32_UNROLL);
+    const dim3 grid = grid_for(L.n, FEWBIT_FWD32_THREADS / kWave, FEWBIT_FWD32_WG_PER_CU, 1);
     (void)hipGetLastError();
-    hipLaunchKernelGGL((fwd32_kernel<BITS, ACT>), grid, dim3(FEWBIT_FWD32_THREADS), 0, L.s,
+    auto kernel = store_nt(4 * L.n) ? fwd32_kernel<BITS, ACT, kNt> : fwd32_kernel<BITS, ACT, kThroughNt>;
+    hipLaunchKernelGGL(kernel, grid, dim3(FEWBIT_FWD32_THREADS), 0, L.s,
                        static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n,
                        nw, table_args(L.t), sym);
   } else {
@@ -1733,7 +1726,8 @@ void launch_fwd(const Launch& L) {
     if (!table) {
       const dim3 grid = grid_for(L.n, FEWBIT_FWD16V_THREADS / kWave, 0, FEWBIT_FWD16V_UNROLL);
       (void)hipGetLastError();
-      hipLaunchKernelGGL((fwd16v_kernel<DT, BITS, ACT>), grid, dim3(FEWBIT_FWD16V_THREADS), 0, L.s,
+      auto kernel = store_nt(2 * L.n) ? fwd16v_kernel<DT, BITS, ACT, kNt> : fwd16v_kernel<DT, BITS, ACT, kThroughNt>;
+      hipLaunchKernelGGL(kernel, grid, dim3(FEWBIT_FWD16V_THREADS), 0, L.s,
                          static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes,
                          L.n, nw, table_args(L.t), sym);
     } else if (holds) {
@@ -1782,7 +1776,8 @@ void launch_bwd(const Launch& L) {
   (void)hipGetLastError();
   if constexpr (DT == FEWBIT_F32) {
     const dim3 grid = grid_for(L.n, FEWBIT_BWD32_THREADS / kWave, 0, FEWBIT_BWD32_UNROLL);
-    hipLaunchKernelGGL((bwd32_kernel<BITS>), grid, dim3(FEWBIT_BWD32_THREADS), 0, L.s,
+    auto kernel = store_nt(4 * L.n) ? bwd32_kernel<BITS, kNt> : bwd32_kernel<BITS, kThrough>;
+    hipLaunchKernelGGL(kernel, grid, dim3(FEWBIT_BWD32_THREADS), 0, L.s,
                        static_cast<const float*>(L.in), L.codes, static_cast<float*>(L.out), L.n,
                        nw, table_args(L.t));
   } else {
@@ -1792,7 +1787,8 @@ void launch_bwd(const Launch& L) {
     int64_t units = (full + run - 1) / run * run;
     if (L.n % kTile != 0 && units <= BwdOrder<BITS>::unit_of_tile(full)) units = BwdOrder<BITS>::unit_of_tile(full) + 1;
     const dim3 grid = grid_for(units * kTile, 1, 0, 1);
-    hipLaunchKernelGGL((bwd_kernel<DT, BITS>), grid, dim3(kWave), 0, L.s,
+    auto kernel = store_nt(2 * L.n) ? bwd_kernel<DT, BITS, kNt> : bwd_kernel<DT, BITS, kThrough>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kWave), 0, L.s,
                        static_cast<const uint16_t*>(L.in), L.codes, static_cast<uint16_t*>(L.out),
                        L.n, nw, table_args(L.t));
   }
