@@ -1,9 +1,13 @@
-"""ctypes binding of libfewbit.so (the C ABI declared in include/fewbit.h).
+"""Binding of libfewbit.so (the C ABI declared in include/fewbit.h).
 
 Argument marshalling only: every step of the forward and backward runs in
 the library's HIP kernels; PyTorch supplies device memory and the stream.
-There is no fallback: if the shared library is missing or fails to load,
+There is no fallback: if a shared library is missing or fails to load,
 importing this module raises.
+
+fwd and bwd on ordinary device tensors go through _native.so (C++: checks,
+allocations, stream and launch in one call); every other argument takes the
+path through ctypes here, which raises what a wrong argument raises.
 """
 from __future__ import annotations
 
@@ -78,6 +82,18 @@ def _load():
 
 
 lib = _load()
+
+
+def _load_native():
+    try:
+        from . import _native
+    except ImportError as e:
+        raise ImportError("_native.so is missing or does not load: build it with "
+                          "`python -m paper_2202_00441_amd.build`") from e
+    return _native
+
+
+_native = _load_native()
 
 
 def strerror(status: int) -> str:
@@ -247,6 +263,11 @@ def fwd(table: Table, x, y=None, codes=None):
     size) before the call, so a wrong buffer raises instead of reaching the
     kernels.
     """
+    r = _native.fwd(table.c, x, y, codes)
+    if r is not None:
+        if type(r) is int:
+            raise FewbitError(r, "fewbit_fwd")
+        return r
     import torch
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous device tensor")
@@ -275,6 +296,11 @@ def bwd(table: Table, grad_out, codes, grad_in=None):
     codes must hold at least packed_words(grad_out.numel(), bits) words on
     grad_out's device; codes and grad_in (if passed) are checked before the
     call."""
+    r = _native.bwd(table.c, grad_out, codes, grad_in)
+    if r is not None:
+        if type(r) is int:
+            raise FewbitError(r, "fewbit_bwd")
+        return r
     import torch
     if not grad_out.is_cuda or not grad_out.is_contiguous():
         raise ValueError("grad_out must be a contiguous device tensor")
@@ -291,3 +317,11 @@ def bwd(table: Table, grad_out, codes, grad_in=None):
     if rc != OK:
         raise FewbitError(rc, "fewbit_bwd")
     return grad_in
+
+
+def _bwd_of_bytes(table: bytes, grad_out, codes):
+    """bwd for the native autograd node, which keeps a copy of the table."""
+    return bwd(Table(CTable.from_buffer_copy(table)), grad_out.contiguous(), codes)
+
+
+_native.set_general(_bwd_of_bytes, FewbitError)

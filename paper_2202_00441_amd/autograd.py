@@ -4,7 +4,7 @@ from __future__ import annotations
 
 import torch
 
-from ._lib import ACTS, Table, Weight, W_NORMAL, bwd, fit_table, fwd
+from ._lib import ACTS, FewbitError, Table, Weight, W_NORMAL, _native, bwd, fit_table, fwd
 
 
 class FewBitActivation(torch.autograd.Function):
@@ -42,7 +42,14 @@ class FewBitAct(torch.nn.Module):
         self.table = table
 
     def forward(self, x):
-        return FewBitActivation.apply(x, self.table)
+        # ordinary device tensors: the same function as a C++ autograd node
+        # (None: not one of those)
+        y = _native.activation(self.table.c, x)
+        if y is None:
+            return FewBitActivation.apply(x, self.table)
+        if type(y) is int:
+            raise FewbitError(y, "fewbit_fwd")
+        return y
 
     def extra_repr(self) -> str:
         return f"act={self.act}, bits={self.bits}"

@@ -1,4 +1,5 @@
-"""Build libfewbit.so (HIP kernels for gfx950 + host fit + C ABI) in-tree.
+"""Build libfewbit.so (HIP kernels for gfx950 + host fit + C ABI) and _native.so
+(the calls on torch tensors, host code linked against it) in-tree.
 
     python -m paper_2202_00441_amd.build      # or: python paper_2202_00441_amd/build.py
 
@@ -27,9 +28,37 @@ FLAGS = [
 ]
 
 
+NATIVE_OUT = os.path.join(HERE, "_native.so")
+NATIVE_SOURCE = os.path.join(CSRC, "binding.cpp")
+CXX = os.environ.get("CXX", "g++")
+
+
 def build(verbose: bool = False, extra=()) -> str:
-    tmp = OUT + ".tmp"
-    cmd = [HIPCC, *FLAGS, *extra, "-o", tmp, *SOURCES]
+    _compile([HIPCC, *FLAGS, *extra, "-o", OUT + ".tmp", *SOURCES], OUT, verbose)
+    build_native(verbose)            # links libfewbit.so, so after it
+    return OUT
+
+
+def build_native(verbose: bool = False) -> str:
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    includes = [os.path.join(ROOT, "include"), *include_paths(), os.path.join(rocm, "include"),
+                sysconfig.get_paths()["include"]]
+    _compile([CXX, "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall",
+              # the HIP headers ask for the platform where hipcc does not compile
+              "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+              f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+              *(f"-I{d}" for d in includes), "-o", NATIVE_OUT + ".tmp", NATIVE_SOURCE,
+              f"-L{HERE}", "-lfewbit", f"-L{libs}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip",
+              "-ltorch_python", "-Wl,-rpath,$ORIGIN"], NATIVE_OUT, verbose)
+    return NATIVE_OUT
+
+
+def _compile(cmd, out: str, verbose: bool) -> None:
+    tmp = out + ".tmp"
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -37,11 +66,10 @@ def build(verbose: bool = False, extra=()) -> str:
     msgs = [ln for ln in (r.stdout + r.stderr).splitlines()
             if "packed-fp32-ops" not in ln and ln.strip()]
     if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n" + "\n".join(msgs))
     if verbose and msgs:
         print("\n".join(msgs))
-    os.replace(tmp, OUT)
-    return OUT
+    os.replace(tmp, out)
 
 
 if __name__ == "__main__":
