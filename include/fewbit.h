@@ -182,16 +182,17 @@ int fewbit_fwd(const fewbit_table* t, int32_t dtype, const void* x, void* y,
  * looked up per input bit pattern in tables each workgroup puts in LDS);
  * below it, the per-element kernel (f and the compares evaluated for every
  * element).  The count depends on the activation, the bit width and the
- * type (dtype FEWBIT_F16 or FEWBIT_BF16); INT64_MAX where the per-element
- * kernel runs at every size.  bf16 forwards of 6 to 8 Mi elements use the
- * table kernel at every bit width; the count is that of bf16 tables whose
- * boundaries are 0 or of ordinary size (2^-9 to 15 in magnitude): others
- * switch at larger sizes.  All kernels give results within the same
- * bounds: indices and codes identical, y within one unit in the last place
- * of the correctly rounded f.  This only tells a caller (or a test) which
- * kernel a given n reaches.  Returns -1 for an unknown activation, bits
- * outside 1..4, or another type.  Host only, no device access.  (A query of
- * the library's dispatch, not an operation of the paper.) */
+ * type (dtype FEWBIT_F16 or FEWBIT_BF16); INT64_MAX for the per-element
+ * kernel at every size.  Below the count, bf16 forwards of 3 to 8 Mi
+ * elements use the table kernel too at 3 and 4 bits.  The count of bf16 is
+ * that of tables whose boundaries are 0 or of ordinary size (2^-9 to 15 in
+ * magnitude); others switch at larger sizes.  All kernels give results
+ * within the same bounds: indices and codes identical, y within one unit in
+ * the last place of the correctly rounded f.  This only tells a caller (or
+ * a test) which kernel a given n reaches.  Returns -1 for an unknown
+ * activation, bits outside 1..4, or another type.  Host only, no device
+ * access.  (A query of the library's dispatch, not an operation of the
+ * paper.) */
 int64_t fewbit_fwd16_table_min(int32_t act, int32_t bits, int32_t dtype);
 
 /*

@@ -7,6 +7,9 @@ Flags:
   --offload-arch=gfx950         MI355X only, one code path
   -O3, no fast-math             IEEE fp32 semantics, denormals kept
   -packed-fp32-ops disabled     no packed fp32 VALU forms are generated
+  kernarg preload               pointers and size arrive in scalar registers with the wave:
+                                its first loads wait for no load of their addresses
+  constexpr steps               the bf16 output factors are evaluated at compile time
 """
 import os
 import subprocess
@@ -23,7 +26,7 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-fno-gpu-flush-denormals-to-zero", "-fno-fast-math", "-ffp-contract=on",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-fconstexpr-steps=200000000",
+    "-fconstexpr-steps=200000000", "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-I", os.path.join(ROOT, "include"),
 ]
 

@@ -19,11 +19,10 @@
 // Each packed word has one value, written by its lane (and by lanes that
 // store an identical copy, so that full tiles need no masking).
 //
-// Streams are read and written with non-temporal 16-byte buffer accesses
-// (nothing is reused).  Most kernels run one wave per tile (the per-element
-// fp16 / bf16 forward one wave per two tiles) and let the hardware
-// dispatcher balance the compute units; the forward with full-range tables is
-// persistent (see the launch-shape knobs below).
+// Streams are read and written with 16-byte buffer accesses, read
+// non-temporally (nothing is reused).  Most kernels run one wave per tile and
+// let the hardware dispatcher balance the compute units; the forward with
+// full-range tables is persistent (see the launch-shape knobs below).
 //
 // fp16 / bf16 forward.  Output pattern and interval index are functions of
 // the 16-bit input pattern alone.  bf16 (fwd16_kernel): the few thousand
@@ -50,16 +49,14 @@
 #include "fwd16_out.h"
 #include "fwd16_rules.h"
 
-// Launch-shape knobs (compile time): threads per workgroup, workgroups per
-// CU and tiles per wave and loop trip, per kernel.  A positive WG_PER_CU
-// caps the grid at that many workgroups per compute unit, and waves then walk
-// the tiles (persistent); 0 launches one wave per tile group, and the
-// hardware dispatcher hands out workgroups as earlier ones finish.  The
-// dispatcher balances the load between compute units, whose streaming rates
-// differ by a few per cent from one to another; a persistent grid ends only
-// when its slowest unit has walked its share.  The full-range table forward
-// holds 160 KiB of tables per workgroup (all of a CU's LDS), built at its
-// start, so it is persistent with one workgroup per CU.
+// Launch-shape knobs of the full-range table forward (compile time): threads
+// per workgroup, workgroups per CU, and tiles per wave and loop trip.  It holds
+// 160 KiB of tables per workgroup (all of a CU's LDS), built at its start, so
+// it is persistent with one workgroup per CU, whose waves walk the tiles; it
+// ends only when its slowest compute unit has walked its share.  Every other
+// kernel launches its waves once, and the dispatcher hands out workgroups as
+// earlier ones finish, which balances the load between compute units, whose
+// streaming rates differ by a few per cent.
 #ifndef FEWBIT_FWD16_THREADS
 #define FEWBIT_FWD16_THREADS 512
 #endif
@@ -68,26 +65,6 @@
 #endif
 #ifndef FEWBIT_FWD16_UNROLL
 #define FEWBIT_FWD16_UNROLL 4
-#endif
-// the fp16 / bf16 forward by evaluation (no tables): threads per workgroup,
-// and tiles per wave loaded together before they are evaluated
-#ifndef FEWBIT_FWD16V_THREADS
-#define FEWBIT_FWD16V_THREADS 64
-#endif
-#ifndef FEWBIT_FWD16V_UNROLL
-#define FEWBIT_FWD16V_UNROLL 2
-#endif
-#ifndef FEWBIT_FWD32_THREADS
-#define FEWBIT_FWD32_THREADS 256
-#endif
-#ifndef FEWBIT_FWD32_WG_PER_CU
-#define FEWBIT_FWD32_WG_PER_CU 0
-#endif
-#ifndef FEWBIT_BWD32_THREADS
-#define FEWBIT_BWD32_THREADS 256
-#endif
-#ifndef FEWBIT_BWD32_UNROLL
-#define FEWBIT_BWD32_UNROLL 1
 #endif
 
 namespace {
@@ -671,6 +648,9 @@ __device__ inline uint32_t load_field_full(const Span& base, int lane) {
   }
 }
 
+// packed words of n codes
+__host__ __device__ inline int64_t words_of(int64_t n, int bits) { return (n * bits + 31) / 32; }
+
 struct WaveIndex {
   int lane;
   int64_t wave, nwaves;
@@ -926,20 +906,24 @@ __global__ __launch_bounds__(FEWBIT_FWD16_THREADS) void fwd16full_kernel(
 }
 
 // fp16 / bf16 forward by evaluation: f and the compares for every element,
-// no tables.  The table kernel above builds its tables in every workgroup
-// and runs a persistent grid; below the sizes of kTableMinLog2 this kernel,
-// with no setup and a dispatcher-balanced grid of two-tile waves, is
-// faster.  Where the table kernel evaluates f (the blocks no rule covers) it
+// no tables.  Bound by HBM where f and the compares take up to about 16 VALU
+// slots an element (every activation at 1 and most at 2 bits), by VALU beyond.
+// Where the full-range table kernel evaluates f (the blocks no rule covers) it
 // uses this same f and rounding.
 //
-// The full tiles of one wave: y from the fp32 f, and the codes shifted into
-// the lane's field from its last element to its first (element j of the
-// lane's 8 at bits BITS j).  SYM: the table is symmetric, the index is that
-// of |x|.  The wave takes its tiles in groups of U consecutive ones and
-// issues all U loads before it evaluates the first, so its next loads are in
-// flight while it computes (one tile per wave leaves the memory idle during
-// the evaluation, which is long next to the streaming); the whole tiles past
-// the last group go one at a time.
+// One tile per one-wave workgroup, and nothing between the wave's start and its
+// stream load: pointers and size arrive in scalar registers with the wave
+// (kernarg preload), there is no loop over the grid, and the boundaries are
+// read after the load has gone out.  So the dispatcher alone keeps the memory
+// busy: fp16 SiLU 2 bits of 51.4M elements 34.9 -> 32.3 us (84% of 8 TB/s)
+// against two tiles per wave in a loop with its boundaries read first, bf16
+// SELU 2 bits of 34M 26.5 -> 23.5, fp16 Sigmoid 1 bit of 2^27 86.7 -> 80.5; and
+// half the evaluation in series on small tensors (12 fp16 Tanh layers of 2^14,
+// 4 bits, with their backwards in a graph: 76 -> 58 us).
+//
+// A full tile: y from the fp32 f, and the codes shifted into the lane's field
+// from its last element to its first (element j of the lane's 8 at bits
+// BITS j).  SYM: the table is symmetric, the index is that of |x|.
 template <int DT, int BITS, int ACT, bool SYM>
 __device__ inline void fwd16v_tile(u32x4_t in, const Search<BITS>& cl, u32x4_t& out, uint32_t& F) {
   using H = Half<DT>;
@@ -954,55 +938,29 @@ __device__ inline void fwd16v_tile(u32x4_t in, const Search<BITS>& cl, u32x4_t& 
 }
 
 template <int DT, int BITS, int ACT, bool SYM, int P>
-__device__ inline void fwd16v_tiles(const uint16_t* x, uint16_t* y, uint32_t* codes, int64_t full,
-                                    const WaveIndex& wi, const Search<BITS>& cl) {
-  constexpr int U = FEWBIT_FWD16V_UNROLL;
+__global__ __launch_bounds__(kWave) void fwd16v_kernel(
+    const uint16_t* x, uint16_t* y, uint32_t* __restrict__ codes, int64_t n, TableArgs tab) {
   constexpr int kWords = 16 * BITS;
-  const uint32_t lane_b = static_cast<uint32_t>(wi.lane) * kLaneBytes;
-  const int64_t groups = full / U;
-  for (int64_t g = wi.wave; g < groups; g += wi.nwaves) {
-    const int64_t t0 = g * U;
-    u32x4_t in[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) in[u] = Span(x + (t0 + u) * kTile, kSpanBytes).ld16(lane_b);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      u32x4_t out;
-      uint32_t F;
-      fwd16v_tile<DT, BITS, ACT, SYM>(in[u], cl, out, F);
-      OutSpan<P>(y + (t0 + u) * kTile, kSpanBytes).st16(lane_b, out);
-      pack_store_full<BITS>(OutSpan<P>(codes + (t0 + u) * kWords, kWords * 4), F, wi.lane);
-    }
-  }
-  for (int64_t t = groups * U + wi.wave; t < full; t += wi.nwaves) {
+  const int lane = static_cast<int>(threadIdx.x);
+  const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
+  const int64_t full = static_cast<int64_t>(static_cast<uint64_t>(n) / kTile);
+  const int64_t t = blockIdx.x;
+  // of a tile that is not whole nothing is loaded here (0 bytes)
+  const u32x4_t in = Span(x + t * kTile, t < full ? kSpanBytes : 0u).ld16(lane_b);
+  // the stream load is in flight before the boundaries are put in place
+  __builtin_amdgcn_sched_barrier(0);
+  const Search<BITS> cl(tab, lane, SYM);
+  if (t < full) {
     u32x4_t out;
     uint32_t F;
-    fwd16v_tile<DT, BITS, ACT, SYM>(Span(x + t * kTile, kSpanBytes).ld16(lane_b), cl, out, F);
+    fwd16v_tile<DT, BITS, ACT, SYM>(in, cl, out, F);
     OutSpan<P>(y + t * kTile, kSpanBytes).st16(lane_b, out);
-    pack_store_full<BITS>(OutSpan<P>(codes + t * kWords, kWords * 4), F, wi.lane);
-  }
-}
-
-template <int DT, int BITS, int ACT, int P>
-__global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
-    const uint16_t* x, uint16_t* y, uint32_t* __restrict__ codes, int64_t n, int64_t nwords,
-    TableArgs tab, int symmetric) {
-  constexpr int kWords = 16 * BITS;
-  const WaveIndex wi = wave_index<FEWBIT_FWD16V_THREADS>();
-  const Search<BITS> cl(tab, wi.lane, symmetric);
-  const int64_t full = n / kTile;
-  const int64_t lane_off = static_cast<int64_t>(wi.lane) * kPerLane;
-  if (symmetric)
-    fwd16v_tiles<DT, BITS, ACT, true, P>(x, y, codes, full, wi, cl);
-  else
-    fwd16v_tiles<DT, BITS, ACT, false, P>(x, y, codes, full, wi, cl);
-  // the partial tile at the end, if any, goes to the wave that would own it
-  if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
-    const int64_t t = full;
+    pack_store_full<BITS>(OutSpan<P>(codes + t * kWords, kWords * 4), F, lane);
+  } else {                                       // the partial tile at the end
     uint32_t F = 0;
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
-      const int64_t e = t * kTile + lane_off + j;
+      const int64_t e = full * kTile + lane * kPerLane + j;
       const float v = e < n ? Half<DT>::widen(x[e]) : 0.0f;
       const uint32_t c = cl.code(v);                          // all lanes
       if (e < n) {
@@ -1010,8 +968,8 @@ __global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
         F |= c << (BITS * j);
       }
     }
-    const int64_t wbase = t * kWords;
-    pack_store<BITS>(OutSpan<P>(codes + wbase, kWords * 4), F, wi.lane, nwords - wbase);
+    const int64_t wbase = full * kWords;
+    pack_store<BITS>(OutSpan<P>(codes + wbase, kWords * 4), F, lane, words_of(n, BITS) - wbase);
   }
 }
 
@@ -1031,11 +989,11 @@ __global__ __launch_bounds__(FEWBIT_FWD16V_THREADS) void fwd16v_kernel(
 // between need no search.
 //
 // Measured (GELU, 3 bits, back-to-back launches; the full-range table kernel,
-// the per-element kernel, this one): 2^23 elements 12.0, 9.9, 7.0 us; 12.6M
-// 14.8, 13.5, 11.5; 2^26 53.4, 57.0, 49.0; 2^28 202, 219, 186 (78.9% of
-// 8 TB/s; moving the same bytes with no work 182).  Two tiles per wave: one
-// leaves the table's cost on too few elements (2^28: 213 us in a probe), four
-// leave the last workgroups of a CU alone for longer (201).
+// the per-element kernel, this one): 2^23 elements 12.0, 8.9, 7.5 us; 12.6M
+// 14.8, 11.7, 10.8; 2^26 53.4, 52.4, 47.2; 2^28 202, 205, 175 (83.7% of
+// 8 TB/s).  Two tiles per wave: one leaves the table's cost on too few elements
+// (2^28: 213 us in a probe where two took 191), four leave the last workgroups
+// of a CU alone for longer (201).
 constexpr int kTabUnroll = 2;
 
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
@@ -1262,6 +1220,14 @@ __device__ inline uint32_t load_field32(const Span& base, int v, int lane, int64
   return __builtin_amdgcn_alignbit(hi, lo, b0 & 31) & C::kMask;
 }
 
+// One tile per wave, kThreads32 threads per workgroup.
+constexpr int kThreads32 = 256;
+
+__device__ inline int64_t tile32() {
+  return static_cast<int64_t>(blockIdx.x) * (kThreads32 / kWave) +
+         __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
+}
+
 // ---------------------------------------------------------------- forward, fp32
 template <int BITS, int ACT>
 __device__ inline void fwd32_half(u32x4_t in, const Search<BITS>& cl, u32x4_t& out, uint32_t& f) {
@@ -1275,36 +1241,34 @@ __device__ inline void fwd32_half(u32x4_t in, const Search<BITS>& cl, u32x4_t& o
 }
 
 template <int BITS, int ACT, int P>
-__global__ __launch_bounds__(FEWBIT_FWD32_THREADS) void fwd32_kernel(
-    const float* x, float* y, uint32_t* __restrict__ codes, int64_t n, int64_t nwords,
-    TableArgs tab, int symmetric) {
+__global__ __launch_bounds__(kThreads32) void fwd32_kernel(
+    const float* x, float* y, uint32_t* __restrict__ codes, int64_t n, int32_t symmetric, TableArgs tab) {
   constexpr int kWords = Codes32<BITS>::kWords;
-  const WaveIndex wi = wave_index<FEWBIT_FWD32_THREADS>();
-  const Search<BITS> cl(tab, wi.lane, symmetric);
-  const int64_t full = n / kTile;
-  const int64_t lane_off = static_cast<int64_t>(wi.lane) * 4;
-  const uint32_t lane_b = static_cast<uint32_t>(wi.lane) * kLaneBytes;
-
-  for (int64_t t = wi.wave; t < full; t += wi.nwaves) {
-    u32x4_t in[2], out[2];
-    uint32_t f[2];
+  const int lane = static_cast<int>(threadIdx.x & (kWave - 1));
+  const int64_t full = static_cast<int64_t>(static_cast<uint64_t>(n) / kTile);
+  const int64_t t = tile32();
+  const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
+  u32x4_t in[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) in[h] = Span(x + t * kTile + h * 256, kSpanBytes).ld16(lane_b);
+  for (int h = 0; h < 2; ++h) in[h] = Span(x + t * kTile + h * 256, t < full ? kSpanBytes : 0u).ld16(lane_b);
+  // the stream loads are in flight before the boundaries are put in place
+  __builtin_amdgcn_sched_barrier(0);
+  const Search<BITS> cl(tab, lane, symmetric);
+  if (t < full) {
+    u32x4_t out[2];
+    uint32_t f[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) fwd32_half<BITS, ACT>(in[h], cl, out[h], f[h]);
 #pragma unroll
     for (int h = 0; h < 2; ++h) OutSpan<P>(y + t * kTile + h * 256, kSpanBytes).st16(lane_b, out[h]);
-    pack_store32<BITS, true>(OutSpan<P>(codes + t * kWords, kWords * 4), f[0], f[1], wi.lane, kWords);
-  }
-  // the partial tile at the end, if any, goes to the wave that would own it
-  if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
-    const int64_t t = full;
+    pack_store32<BITS, true>(OutSpan<P>(codes + t * kWords, kWords * 4), f[0], f[1], lane, kWords);
+  } else if (t == full && n % kTile != 0) {      // the partial tile at the end
     uint32_t f[2] = {0u, 0u};
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int64_t e = t * kTile + h * 256 + lane_off + j;
+        const int64_t e = t * kTile + h * 256 + lane * 4 + j;
         const float xv = e < n ? x[e] : 0.0f;
         const uint32_t c = cl.code(xv);                     // all lanes
         if (e < n) {
@@ -1313,7 +1277,7 @@ __global__ __launch_bounds__(FEWBIT_FWD32_THREADS) void fwd32_kernel(
         }
       }
     const int64_t wbase = t * kWords;
-    pack_store32<BITS, false>(OutSpan<P>(codes + wbase, kWords * 4), f[0], f[1], wi.lane, nwords - wbase);
+    pack_store32<BITS, false>(OutSpan<P>(codes + wbase, kWords * 4), f[0], f[1], lane, words_of(n, BITS) - wbase);
   }
 }
 
@@ -1399,47 +1363,31 @@ struct BwdOrder {
 };
 
 template <int DT, int BITS, int P>
-__device__ inline void bwd16_full_tile(const uint16_t* g, const uint32_t* codes, uint16_t* gin,
-                                       int64_t t, int lane, const TableArgs& tab) {
-  constexpr int kWords = 16 * BITS;
-  const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
-  const u32x4_t in = Span(g + t * kTile, kSpanBytes).ld16(lane_b);
-  const uint32_t F = load_field_full<BITS>(Span(codes + t * kWords, kWords * 4), lane);
-  // the stream loads are in flight before the values are put in place
-  __builtin_amdgcn_sched_barrier(0);
-  const Values<BITS> val(tab);
-  OutSpan<P>(gin + t * kTile, kSpanBytes).st16(lane_b, grad16_tile<DT, BITS>(in, F, val));
-}
-
-template <int DT, int BITS, int P>
 __global__ __launch_bounds__(kWave) void bwd_kernel(
-    const uint16_t* g, const uint32_t* __restrict__ codes, uint16_t* gin, int64_t n,
-    int64_t nwords, TableArgs tab) {
+    const uint16_t* g, const uint32_t* __restrict__ codes, uint16_t* gin, int64_t n, TableArgs tab) {
   constexpr int kWords = 16 * BITS;
   constexpr uint32_t kMask = (1u << BITS) - 1u;
-  constexpr int64_t kRun = BwdOrder<BITS>::kRun;
-  const WaveIndex wi = wave_index<kWave>();
-  const int64_t full = n / kTile;
-  const int64_t units = (full + kRun - 1) / kRun * kRun;
-
-  // one unit per wave unless the grid was capped (see grid_for)
-  for (int64_t u = wi.wave; u < units; u += wi.nwaves) {
-    const int64_t t = BwdOrder<BITS>::tile_of_unit(u);
-    if (t < full) bwd16_full_tile<DT, BITS, P>(g, codes, gin, t, wi.lane, tab);
-  }
-  // the partial tile at the end, if any, goes to the wave of its unit
-  if (n % kTile != 0 && wi.wave == BwdOrder<BITS>::unit_of_tile(full) % wi.nwaves) {
+  const int lane = static_cast<int>(threadIdx.x);
+  const int64_t full = static_cast<int64_t>(static_cast<uint64_t>(n) / kTile);
+  const int64_t t = BwdOrder<BITS>::tile_of_unit(blockIdx.x);
+  if (t < full) {
+    const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
+    const u32x4_t in = Span(g + t * kTile, kSpanBytes).ld16(lane_b);
+    const uint32_t F = load_field_full<BITS>(Span(codes + t * kWords, kWords * 4), lane);
+    // the stream loads are in flight before the values are put in place
+    __builtin_amdgcn_sched_barrier(0);
     const Values<BITS> val(tab);
-    const int64_t t = full;
+    OutSpan<P>(gin + t * kTile, kSpanBytes).st16(lane_b, grad16_tile<DT, BITS>(in, F, val));
+  } else if (t == full && n % kTile != 0) {      // the partial tile at the end
+    const Values<BITS> val(tab);
     const int64_t wbase = t * kWords;
-    const int64_t lane_off = static_cast<int64_t>(wi.lane) * kPerLane;
-    const uint32_t F = load_field<BITS>(Span(codes + wbase, kWords * 4), wi.lane, nwords - wbase);
+    const uint32_t F = load_field<BITS>(Span(codes + wbase, kWords * 4), lane, words_of(n, BITS) - wbase);
     float v[kPerLane];
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) v[j] = val((F >> (BITS * j)) & kMask);   // all lanes
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
-      const int64_t e = t * kTile + lane_off + j;
+      const int64_t e = t * kTile + lane * kPerLane + j;
       if (e < n) Scalar<DT>::store(gin, e, Scalar<DT>::load(g, e) * v[j]);
     }
   }
@@ -1457,56 +1405,40 @@ __device__ inline u32x4_t grad32_half(u32x4_t g, uint32_t f, const Values<BITS>&
 }
 
 template <int BITS, int P>
-__global__ __launch_bounds__(FEWBIT_BWD32_THREADS) void bwd32_kernel(
-    const float* g, const uint32_t* __restrict__ codes, float* gin, int64_t n, int64_t nwords,
-    TableArgs tab) {
-  constexpr int U = FEWBIT_BWD32_UNROLL;
+__global__ __launch_bounds__(kThreads32) void bwd32_kernel(
+    const float* g, const uint32_t* __restrict__ codes, float* gin, int64_t n, TableArgs tab) {
   constexpr int kWords = Codes32<BITS>::kWords;
   constexpr uint32_t kMask = (1u << BITS) - 1u;
-  const WaveIndex wi = wave_index<FEWBIT_BWD32_THREADS>();
-  const Values<BITS> val(tab);
-  const int64_t full = n / kTile;
-  const int64_t groups = full / U;
-  const int64_t lane_off = static_cast<int64_t>(wi.lane) * 4;
-  const uint32_t lane_b = static_cast<uint32_t>(wi.lane) * kLaneBytes;
-
-  for (int64_t gi = wi.wave; gi < groups; gi += wi.nwaves) {
-    const int64_t t0 = gi * U;
-    u32x4_t in[U][2];
-    uint32_t f[U][2];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        in[u][h] = Span(g + (t0 + u) * kTile + h * 256, kSpanBytes).ld16(lane_b);
-        f[u][h] = load_field32<BITS, true>(Span(codes + (t0 + u) * kWords, kWords * 4), h, wi.lane, kWords);
-      }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        OutSpan<P>(gin + (t0 + u) * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in[u][h], f[u][h], val));
-  }
-  for (int64_t t = groups * U + wi.wave; t < full; t += wi.nwaves) {
+  const int lane = static_cast<int>(threadIdx.x & (kWave - 1));
+  const int64_t full = static_cast<int64_t>(static_cast<uint64_t>(n) / kTile);
+  const int64_t t = tile32();
+  if (t < full) {
+    const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
+    u32x4_t in[2];
+    uint32_t f[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const u32x4_t in = Span(g + t * kTile + h * 256, kSpanBytes).ld16(lane_b);
-      const uint32_t f = load_field32<BITS, true>(Span(codes + t * kWords, kWords * 4), h, wi.lane, kWords);
-      OutSpan<P>(gin + t * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in, f, val));
+      in[h] = Span(g + t * kTile + h * 256, kSpanBytes).ld16(lane_b);
+      f[h] = load_field32<BITS, true>(Span(codes + t * kWords, kWords * 4), h, lane, kWords);
     }
-  }
-  if (n % kTile != 0 && wi.wave == full % wi.nwaves) {
-    const int64_t t = full;
+    // the stream loads are in flight before the values are put in place
+    __builtin_amdgcn_sched_barrier(0);
+    const Values<BITS> val(tab);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      OutSpan<P>(gin + t * kTile + h * 256, kSpanBytes).st16(lane_b, grad32_half<BITS>(in[h], f[h], val));
+  } else if (t == full && n % kTile != 0) {      // the partial tile at the end
+    const Values<BITS> val(tab);
     const int64_t wbase = t * kWords;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const uint32_t f = load_field32<BITS, false>(Span(codes + wbase, kWords * 4), h, wi.lane, nwords - wbase);
+      const uint32_t f = load_field32<BITS, false>(Span(codes + wbase, kWords * 4), h, lane, words_of(n, BITS) - wbase);
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = val((f >> (BITS * j)) & kMask);   // all lanes
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int64_t e = t * kTile + h * 256 + lane_off + j;
+        const int64_t e = t * kTile + h * 256 + lane * 4 + j;
         if (e < n) gin[e] = g[e] * v[j];
       }
     }
@@ -1579,6 +1511,16 @@ dim3 grid_for(int64_t n, int waves_per_block, int wg_per_cu, int unroll) {
   return dim3(static_cast<unsigned>(blocks));
 }
 
+int64_t tiles_of(int64_t n) { return n / kTile + (n % kTile != 0); }
+
+// The grid of a launch with one pass per workgroup over `per` units of its
+// work.  (A launch holds at most 2^32 threads; what needs more is refused by
+// the runtime.)
+dim3 grid_of(int64_t units, int per) {
+  const int64_t blocks = (units + per - 1) / per;
+  return dim3(static_cast<unsigned>(blocks > INT32_MAX ? INT32_MAX : blocks));
+}
+
 // The stream must belong to the current device: the grid size, the output
 // tables and the launch all refer to the current device.
 int check_stream_device(hipStream_t stream) {
@@ -1624,37 +1566,33 @@ OutRuns out_runs() {
 
 // log2 of the element count from which an fp16 forward, or a bf16 one whose
 // boundaries the compact table does not hold, runs the full-range table
-// kernel, by [type: fp16, bf16][activation][bits - 1]; 63: never.  The table
-// kernel builds its tables in every workgroup (7-10 us of fixed cost for
-// bf16, 12-15 us for fp16, whose tables need f in far more blocks) and runs
-// as a persistent grid, which streams at about 72% of the HBM peak; the
-// per-element kernel has no setup and a grid of two-tile waves that streams
-// at up to 79%, but evaluates f and the compares per element.  Measured on
-// MI355X (x ~ N(0, 1), 2^23 .. 2^28 elements, back-to-back launches, the
-// mean after the first quarter): the table kernel from the size where it is
-// ahead at every larger size measured (within 2%).  At 2^28 elements the
-// per-element kernel of 1- and 2-bit codes is 4-8% ahead in such runs, but
-// its rate under sustained load swings by about 15% (it draws more power),
-// while the table kernel's holds: there the table kernel is used (28).
-// Softplus, whose per-element f is the most expensive, switches first.
+// kernel, by [type: fp16, bf16][activation][bits - 1]; 63: never.  That kernel
+// builds its tables in every workgroup (7-10 us of fixed cost for bf16, 12-15
+// us for fp16, whose tables need f in far more blocks) and runs as a persistent
+// grid, which streams at about 72% of the HBM peak whatever f and the bits are;
+// the per-element kernel has no setup and streams at up to 87%, but evaluates f
+// and the compares per element.  Measured on MI355X (x ~ N(0, 1), 2^25 .. 2^28
+// elements, back-to-back launches; per element, table): fp16 GELU 4 bits, 2^26
+// 57.8 and 54.9 us, 2^25 30.1 and 33.2; Tanh 2 bits, 2^27 96.6 and 94.2; SiLU
+// 3 bits, 2^28 177 and 189.
 constexpr uint8_t kTableMinLog2[2][FEWBIT_SOFTPLUS + 1][4] = {
     {   // fp16
-        {28, 28, 26, 27},   // gelu
-        {28, 28, 27, 27},   // silu
-        {28, 63, 26, 27},   // sigmoid
-        {28, 27, 25, 25},   // tanh
-        {28, 28, 28, 63},   // relu
-        {28, 26, 25, 26},   // selu
-        {28, 28, 25, 26},   // softplus
+        {63, 63, 26, 26},   // gelu
+        {63, 63, 63, 27},   // silu
+        {63, 63, 63, 27},   // sigmoid
+        {63, 27, 26, 25},   // tanh
+        {63, 63, 63, 63},   // relu
+        {63, 63, 26, 26},   // selu
+        {63, 63, 26, 26},   // softplus
     },
     {   // bf16
-        {28, 28, 24, 24},   // gelu
-        {28, 28, 25, 26},   // silu
-        {28, 28, 28, 27},   // sigmoid
-        {28, 28, 24, 25},   // tanh
-        {28, 28, 28, 28},   // relu
-        {28, 28, 25, 27},   // selu
-        {28, 28, 24, 24},   // softplus
+        {63, 63, 27, 26},   // gelu
+        {63, 63, 63, 63},   // silu
+        {63, 63, 63, 63},   // sigmoid
+        {63, 63, 26, 26},   // tanh
+        {63, 63, 63, 63},   // relu
+        {63, 63, 63, 27},   // selu
+        {63, 63, 28, 27},   // softplus
     },
 };
 
@@ -1664,37 +1602,43 @@ int64_t table_min_of(int dt, int act, int bits) {
 }
 
 // The same for the bf16 kernel with the compact table, wherever the table's
-// boundaries allow it (fwd16_out::holds): log2 of the element count from
-// which it is ahead, by [activation][bits - 1].  Its cost does not depend on
-// the activation or the bit width, the per-element kernel's does: with 3 and
-// 4 bits it is ahead from 2^22 elements on (GELU 3-bit 6.2 -> 4.8 us, Sigmoid
-// 3-bit, the closest, 5.8 -> 4.9; at 2^21 3.9 -> 4.3), with 1 and 2 bits the
-// per-element kernel streams as fast until sustained load slows it (GELU
-// 1-bit, 2^25: 24.6 and 25.6 us; 2^28: 181 and 176).  SELU's table is the
-// largest, ReLU's f the cheapest but its table needs no factors.
+// boundaries allow it (fwd16_out::holds).  Its cost does not depend on the
+// activation or the bit width, the per-element kernel's does.  Measured as
+// above (per element, table): GELU 3 bits, 2^24 14.8 and 15.0 us, 2^25 27.5 and
+// 25.7, 2^28 205 and 175; Sigmoid 3 bits 13.9 and 14.7, 25.3 and 25.7, 190 and
+// 177; with 1 or 2 bits the per-element kernel streams at 81-87% of the HBM
+// peak and is ahead (GELU 1 bit, 2^28: 160 and 171) or level (2 bits: 171).
 constexpr uint8_t kTabMinLog2[FEWBIT_SOFTPLUS + 1][4] = {
-    {27, 27, 22, 22},   // gelu
-    {27, 27, 22, 22},   // silu
-    {27, 27, 22, 22},   // sigmoid
-    {27, 27, 22, 22},   // tanh
-    {26, 26, 22, 22},   // relu
-    {28, 28, 22, 22},   // selu
-    {28, 27, 22, 22},   // softplus
+    {63, 63, 22, 22},   // gelu
+    {63, 63, 25, 22},   // silu
+    {63, 63, 26, 26},   // sigmoid
+    {63, 63, 22, 22},   // tanh
+    {63, 63, 28, 26},   // relu
+    {63, 63, 22, 22},   // selu
+    {63, 28, 22, 22},   // softplus
 };
 
-int64_t tab_min_of(int act, int bits) { return int64_t{1} << kTabMinLog2[act][bits - 1]; }
+int64_t tab_min_of(int act, int bits) {
+  const int lg = kTabMinLog2[act][bits - 1];
+  return lg >= 63 ? INT64_MAX : int64_t{1} << lg;
+}
 
-// At 1 and 2 bits it is also ahead where its workgroups of 32 tiles about
-// fill the chip's 512 places once: 1-bit GELU at 6, 8 and 9 Mi elements 6.8,
-// 8.6, 9.6 us per element, 6.4, 7.0, 9.5 by the table.
+// At 3 and 4 bits it is ahead for every activation while its workgroups of 32
+// tiles fill the chip's 512 places about once (Sigmoid 3 bits, the closest, at
+// 3, 4, 8 and 10 Mi elements: 5.0, 5.7, 8.4, 9.8 us per element, 4.5, 4.8, 7.8,
+// 9.6 by the table; ReLU 3 bits at 8 and 10 Mi 7.9, 9.1 and 7.2, 9.9).
 bool tab_by_size(int act, int bits, int64_t n) {
-  return n >= tab_min_of(act, bits) || (n >= int64_t{6} << 20 && n <= int64_t{8} << 20);
+  return n >= tab_min_of(act, bits) || (bits >= 3 && n >= int64_t{3} << 20 && n <= int64_t{8} << 20);
 }
 
 // Workgroups of 16 waves that take consecutive tiles below, of 8 waves that
-// share runs of 4 tiles with 7 others from here on: 12.6M elements 11.5 and
-// 12.9 us, 2^25 27.0 and 26.8, 2^28 191 and 186.
+// share runs of 4 tiles with 7 others from here on: GELU 3 bits, 12.6M elements
+// 11.5 and 12.9 us, 2^25 27.0 and 26.8, 2^28 191 and 186.
 constexpr int64_t kTabLargeFrom = int64_t{1} << 25;
+
+// Its launches hold 2^32 threads of 16 elements; the full-range kernel's grid
+// does not grow with the tensor.
+constexpr int64_t kTabUpto = int64_t{1} << 35;
 
 template <int DT, int BITS, int ACT, int THREADS, int RUN>
 void launch_tab(const Launch& L, int64_t nw, int sym) {
@@ -1712,24 +1656,24 @@ void launch_fwd(const Launch& L) {
   const int64_t nw = fewbit_packed_words(L.n, BITS);
   const int sym = (L.t->flags & FEWBIT_FLAG_SYMMETRIC) ? 1 : 0;
   if constexpr (DT == FEWBIT_F32) {
-    const dim3 grid = grid_for(L.n, FEWBIT_FWD32_THREADS / kWave, FEWBIT_FWD32_WG_PER_CU, 1);
-    (void)hipGetLastError();
     auto kernel = store_nt(4 * L.n) ? fwd32_kernel<BITS, ACT, kNt> : fwd32_kernel<BITS, ACT, kThroughNt>;
-    hipLaunchKernelGGL(kernel, grid, dim3(FEWBIT_FWD32_THREADS), 0, L.s,
-                       static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n,
-                       nw, table_args(L.t), sym);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kernel, grid_of(tiles_of(L.n), kThreads32 / kWave), dim3(kThreads32), 0, L.s,
+                       static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n, sym,
+                       table_args(L.t));
   } else {
-    const bool holds = DT == FEWBIT_BF16 && fwd16_out::holds(ACT, sym != 0, L.t->s, (1 << BITS) - 1);
+    const bool holds = DT == FEWBIT_BF16 && L.n < kTabUpto && fwd16_out::holds(ACT, sym != 0, L.t->s, (1 << BITS) - 1);
     const bool by_size = holds ? tab_by_size(ACT, BITS, L.n) : L.n >= table_min_of(DT, ACT, BITS);
     const bool table = (L.t->flags & FEWBIT_FLAG_TABLE_FWD) ||
                        (!(L.t->flags & FEWBIT_FLAG_ELEMENT_FWD) && by_size);
     if (!table) {
-      const dim3 grid = grid_for(L.n, FEWBIT_FWD16V_THREADS / kWave, 0, FEWBIT_FWD16V_UNROLL);
+      const bool nt = store_nt(2 * L.n);
+      auto kernel = sym ? (nt ? fwd16v_kernel<DT, BITS, ACT, true, kNt> : fwd16v_kernel<DT, BITS, ACT, true, kThroughNt>)
+                        : (nt ? fwd16v_kernel<DT, BITS, ACT, false, kNt> : fwd16v_kernel<DT, BITS, ACT, false, kThroughNt>);
       (void)hipGetLastError();
-      auto kernel = store_nt(2 * L.n) ? fwd16v_kernel<DT, BITS, ACT, kNt> : fwd16v_kernel<DT, BITS, ACT, kThroughNt>;
-      hipLaunchKernelGGL(kernel, grid, dim3(FEWBIT_FWD16V_THREADS), 0, L.s,
-                         static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes,
-                         L.n, nw, table_args(L.t), sym);
+      hipLaunchKernelGGL(kernel, grid_of(tiles_of(L.n), 1), dim3(kWave), 0, L.s,
+                         static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes, L.n,
+                         table_args(L.t));
     } else if (holds) {
       if constexpr (DT == FEWBIT_BF16) {
         if (L.n < kTabLargeFrom)
@@ -1772,25 +1716,22 @@ void launch_fwd_bits(const Launch& L) {
 
 template <int DT, int BITS>
 void launch_bwd(const Launch& L) {
-  const int64_t nw = fewbit_packed_words(L.n, BITS);
   (void)hipGetLastError();
   if constexpr (DT == FEWBIT_F32) {
-    const dim3 grid = grid_for(L.n, FEWBIT_BWD32_THREADS / kWave, 0, FEWBIT_BWD32_UNROLL);
     auto kernel = store_nt(4 * L.n) ? bwd32_kernel<BITS, kNt> : bwd32_kernel<BITS, kThrough>;
-    hipLaunchKernelGGL(kernel, grid, dim3(FEWBIT_BWD32_THREADS), 0, L.s,
+    hipLaunchKernelGGL(kernel, grid_of(tiles_of(L.n), kThreads32 / kWave), dim3(kThreads32), 0, L.s,
                        static_cast<const float*>(L.in), L.codes, static_cast<float*>(L.out), L.n,
-                       nw, table_args(L.t));
+                       table_args(L.t));
   } else {
     // one-wave workgroups: a whole number of runs of the tile order over the
-    // full tiles, and one more workgroup when the partial tile's unit lies past them
+    // full tiles, and up to the partial tile's unit when that lies past them
     const int64_t full = L.n / kTile, run = BwdOrder<BITS>::kRun;
     int64_t units = (full + run - 1) / run * run;
     if (L.n % kTile != 0 && units <= BwdOrder<BITS>::unit_of_tile(full)) units = BwdOrder<BITS>::unit_of_tile(full) + 1;
-    const dim3 grid = grid_for(units * kTile, 1, 0, 1);
     auto kernel = store_nt(2 * L.n) ? bwd_kernel<DT, BITS, kNt> : bwd_kernel<DT, BITS, kThrough>;
-    hipLaunchKernelGGL(kernel, grid, dim3(kWave), 0, L.s,
-                       static_cast<const uint16_t*>(L.in), L.codes, static_cast<uint16_t*>(L.out),
-                       L.n, nw, table_args(L.t));
+    hipLaunchKernelGGL(kernel, grid_of(units, 1), dim3(kWave), 0, L.s,
+                       static_cast<const uint16_t*>(L.in), L.codes, static_cast<uint16_t*>(L.out), L.n,
+                       table_args(L.t));
   }
 }
 
