@@ -977,8 +977,9 @@ __global__ __launch_bounds__(kWave) void fwd16v_kernel(
 // One LDS word per input pattern of the octaves that matter (fwd16_out.h):
 // the fp32 output factor, with the interval index in its low 4 bits.  An
 // element costs one ds_read_b32 and about eleven VALU operations at every
-// activation and bit width, the packing included, where evaluating f and the
-// compares takes up to thirty: bound by HBM.
+// activation and bit width, the packing included, and about eight more for its
+// share of placing the table (SQ counters, GELU 3 bits: 19.3), where evaluating
+// f and the compares takes up to thirty.  Bound by HBM, with VALU busy 83%.
 //
 // The table is 14-21 KiB, so 32 waves share a CU and the grid needs no
 // persistent walk: each wave takes kTabUnroll tiles, whose loads are in flight
