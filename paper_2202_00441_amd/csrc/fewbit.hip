@@ -1684,9 +1684,17 @@ hipError_t launch_fwd(const Launch& L) {
       const bool nt = store_nt(2 * L.n);
       auto kernel = sym ? (nt ? fwd16v_kernel<DT, BITS, ACT, true, kNt> : fwd16v_kernel<DT, BITS, ACT, true, kThroughNt>)
                         : (nt ? fwd16v_kernel<DT, BITS, ACT, false, kNt> : fwd16v_kernel<DT, BITS, ACT, false, kThroughNt>);
-      return launch(kernel, grid_of(tiles_of(L.n), 1), kWave, L.s,
-                    static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes, L.n,
-                    table_args(L.t));
+      // a launch holds fewer than 2^32 threads, 64 per tile of 512: longer
+      // tensors go in parts of whole tiles
+      constexpr int64_t kPart = int64_t{1} << 34;
+      for (int64_t at = 0; at < L.n; at += kPart) {
+        const int64_t m = L.n - at < kPart ? L.n - at : kPart;
+        const hipError_t e = launch(kernel, grid_of(tiles_of(m), 1), kWave, L.s,
+                                    static_cast<const uint16_t*>(L.in) + at, static_cast<uint16_t*>(L.out) + at,
+                                    L.codes + at / 32 * BITS, m, table_args(L.t));
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
     }
     if constexpr (DT == FEWBIT_BF16) {
       if (holds)

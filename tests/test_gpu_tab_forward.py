@@ -72,3 +72,29 @@ def test_boundaries_at_the_edges(act, symmetric):
     for s in sets:
         _check(act, 1, s, [0.25, 0.75], pats, symmetric, label=f"s={s}")
     _check(act, 2, [-1.5, 0.0, 1.5], [0.0, 0.25, 0.5, 1.0], pats, symmetric, label="around 0")
+
+
+@pytest.mark.slow
+def test_forward_in_parts():
+    # past 2^34 elements the per-element forward is launched in parts: bf16,
+    # in place (37 GB resident), checked around the seam, at the end and at random
+    n = (1 << 34) + 12345
+    bits, s = 1, [0.25]
+    table = P.Table.from_values(P.ACTS["relu"], bits, s, [0.0, 1.0])
+    print(f"[parts] n={n}", flush=True)
+    x = torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(3))
+    rng = np.random.default_rng(4)
+    idx = np.unique(np.concatenate([np.arange((1 << 34) - 2048, (1 << 34) + 2048), np.arange(n - 3000, n),
+                                    rng.integers(0, n, 100000)]))
+    it = torch.from_numpy(idx).cuda()
+    xs = x[it].view(torch.int16).cpu().numpy().view(np.uint16)
+    _, codes = P.fwd(table, x, y=x)
+    torch.cuda.synchronize()
+    ys = x[it].view(torch.int16).cpu().numpy().view(np.uint16)
+    y_ref, _, idx_ref = O.fwd(OACT["relu"], O.BF16, bits, np.float32(s), xs, want_idx=True)
+    check_y(ys, y_ref, "bf16", "y sampled")
+    words = codes[torch.from_numpy(idx // 32).cuda()].cpu().numpy().view(np.uint32)
+    got = (words >> (idx % 32).astype(np.uint32)) & 1
+    check_exact(got.astype(np.int64), np.asarray(idx_ref).astype(np.int64), "codes sampled")
+    del x, codes
+    torch.cuda.empty_cache()
