@@ -1542,9 +1542,16 @@ int check_stream_device(hipStream_t stream) {
 // layers fits the 256 MB memory-side cache but not the L2, nt alone is (12 fp16
 // SiLU layers of 2^20: 69.8 and 73.7 us).  y is stored nt as well as through
 // (its forward with through alone: 71.3 and 88.5 us on the two passes above),
-// the gradient is not (175.5 and 175.7, and 4.97 against 5.08 at 2^22).
+// a short gradient is not (4.97 against 5.08 us at 2^22).
 constexpr int64_t kNtFrom = int64_t{1} << 20, kNtUpto = int64_t{1} << 24;
 bool store_nt(int64_t bytes) { return bytes >= kNtFrom && bytes < kNtUpto; }
+
+// The gradient up to here is left in the memory-side cache for its reader
+// (fp32 Tanh 3-bit pass of 2^25 elements 85.1 us, with nt 87.8); a longer one
+// does not stay there, and with nt it takes no room from what does (bf16 GELU
+// 3-bit pass of 2^28 359.7 us, with nt 344.3; fp32 Sigmoid 4-bit of 2^26 177.2,
+// 173.8; the fp32 backward alone of 35M 45.4, 44.6).
+constexpr int64_t kGradThroughUpto = int64_t{1} << 27;
 
 struct Launch {
   const fewbit_table* t;
@@ -1734,7 +1741,9 @@ hipError_t launch_fwd_bits(const Launch& L) {
 template <int DT, int BITS>
 hipError_t launch_bwd(const Launch& L) {
   if constexpr (DT == FEWBIT_F32) {
-    auto kernel = store_nt(4 * L.n) ? bwd32_kernel<BITS, kNt> : bwd32_kernel<BITS, kThrough>;
+    auto kernel = store_nt(4 * L.n)             ? bwd32_kernel<BITS, kNt>
+                  : 4 * L.n <= kGradThroughUpto ? bwd32_kernel<BITS, kThrough>
+                                                : bwd32_kernel<BITS, kThroughNt>;
     return launch(kernel, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
                   static_cast<const float*>(L.in), L.codes, static_cast<float*>(L.out), L.n,
                   table_args(L.t));
@@ -1744,7 +1753,9 @@ hipError_t launch_bwd(const Launch& L) {
     const int64_t full = L.n / kTile, run = BwdOrder<BITS>::kRun;
     int64_t units = (full + run - 1) / run * run;
     if (L.n % kTile != 0 && units <= BwdOrder<BITS>::unit_of_tile(full)) units = BwdOrder<BITS>::unit_of_tile(full) + 1;
-    auto kernel = store_nt(2 * L.n) ? bwd_kernel<DT, BITS, kNt> : bwd_kernel<DT, BITS, kThrough>;
+    auto kernel = store_nt(2 * L.n)             ? bwd_kernel<DT, BITS, kNt>
+                  : 2 * L.n <= kGradThroughUpto ? bwd_kernel<DT, BITS, kThrough>
+                                                : bwd_kernel<DT, BITS, kThroughNt>;
     return launch(kernel, grid_of(units, 1), kWave, L.s,
                   static_cast<const uint16_t*>(L.in), L.codes, static_cast<uint16_t*>(L.out), L.n,
                   table_args(L.t));
