@@ -113,17 +113,17 @@ def _kernel_key(name: str):
     m = re.search(r"persist_kernel<([0-9]), ?([0-9])>", name)
     if m:
         return f"ceiling_{ {'0': 'copy', '1': 'fwd', '2': 'bwd'}[m.group(1)]}<persistent>"
-    m = re.search(r"(fwd16v_kernel|fwd16full_kernel|fwd16_kernel|fwd32_kernel|bwd32_kernel|bwd_kernel)<([0-9a-z, ]+)>", name)
+    m = re.search(r"(fwd16v_kernel|fwd16full_kernel|fwd16_kernel|fwd32_kernel|fwd32_small_kernel|bwd32_kernel|bwd32_small_kernel|bwd_kernel)<([0-9a-z, ]+)>", name)
     if not m:
         base = name.replace("(anonymous namespace)::", "").replace("void ", "")
         return base.split("(")[0].strip() or name
     args = [int(a) for a in m.group(2).split(",") if a.strip().isdigit()]
     if m.group(1) in ("fwd16_kernel", "fwd16full_kernel", "fwd16v_kernel"):
         return f"{m.group(1)}<{DT_NAMES[args[0]]},{args[1]},{ACT_NAMES[args[2]]}>"
-    if m.group(1) == "fwd32_kernel":
-        return f"fwd32_kernel<f32,{args[0]},{ACT_NAMES[args[1]]}>"
-    if m.group(1) == "bwd32_kernel":
-        return f"bwd32_kernel<f32,{args[0]}>"
+    if m.group(1) in ("fwd32_kernel", "fwd32_small_kernel"):
+        return f"{m.group(1)}<f32,{args[0]},{ACT_NAMES[args[1]]}>"
+    if m.group(1) in ("bwd32_kernel", "bwd32_small_kernel"):
+        return f"{m.group(1)}<f32,{args[0]}>"
     return f"bwd_kernel<{DT_NAMES[args[0]]},{args[1]}>"
 
 

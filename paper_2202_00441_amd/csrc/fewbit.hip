@@ -1251,20 +1251,26 @@ __device__ inline void fwd32_half(u32x4_t in, const Search<BITS>& cl, u32x4_t& o
   }
 }
 
-template <int BITS, int ACT, int P>
-__global__ __launch_bounds__(kThreads32) void fwd32_kernel(
-    const float* x, float* y, uint32_t* __restrict__ codes, int64_t n, int32_t symmetric, TableArgs tab) {
+// LATE: the boundaries are put in place after the stream loads have gone out.
+template <int BITS, int ACT, int P, bool LATE>
+__device__ inline void fwd32_tile(const float* x, float* y, uint32_t* codes, int64_t n, int32_t symmetric,
+                                  const TableArgs& tab) {
   constexpr int kWords = Codes32<BITS>::kWords;
   const int lane = static_cast<int>(threadIdx.x & (kWave - 1));
   const int64_t full = static_cast<int64_t>(static_cast<uint64_t>(n) / kTile);
   const int64_t t = tile32();
   const uint32_t lane_b = static_cast<uint32_t>(lane) * kLaneBytes;
   u32x4_t in[2];
+  auto load = [&] {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) in[h] = Span(x + t * kTile + h * 256, t < full ? kSpanBytes : 0u).ld16(lane_b);
-  // the stream loads are in flight before the boundaries are put in place
-  __builtin_amdgcn_sched_barrier(0);
+    for (int h = 0; h < 2; ++h) in[h] = Span(x + t * kTile + h * 256, t < full ? kSpanBytes : 0u).ld16(lane_b);
+  };
+  if constexpr (LATE) {
+    load();
+    __builtin_amdgcn_sched_barrier(0);
+  }
   const Search<BITS> cl(tab, lane, symmetric);
+  if constexpr (!LATE) load();
   if (t < full) {
     u32x4_t out[2];
     uint32_t f[2];
@@ -1289,6 +1295,20 @@ __global__ __launch_bounds__(kThreads32) void fwd32_kernel(
     const int64_t wbase = t * kWords;
     pack_store32<BITS, false>(OutSpan<P>(codes + wbase, kWords * 4), f[0], f[1], lane, words_of(n, BITS) - wbase);
   }
+}
+
+template <int BITS, int ACT, int P>
+__global__ __launch_bounds__(kThreads32) void fwd32_kernel(
+    const float* x, float* y, uint32_t* __restrict__ codes, int64_t n, int32_t symmetric, TableArgs tab) {
+  fwd32_tile<BITS, ACT, P, true>(x, y, codes, n, symmetric, tab);
+}
+
+// The shortest launches (small32): the structure comes first, so nothing is
+// preloaded (the preload takes the leading pointers and integers only).
+template <int BITS, int ACT>
+__global__ __launch_bounds__(kThreads32) void fwd32_small_kernel(
+    TableArgs tab, const float* x, float* y, uint32_t* __restrict__ codes, int64_t n, int32_t symmetric) {
+  fwd32_tile<BITS, ACT, kNt, false>(x, y, codes, n, symmetric, tab);
 }
 
 // ---------------------------------------------------------------- backward
@@ -1418,8 +1438,7 @@ __device__ inline u32x4_t grad32_half(u32x4_t g, uint32_t f, const Values<BITS>&
 }
 
 template <int BITS, int P>
-__global__ __launch_bounds__(kThreads32) void bwd32_kernel(
-    const float* g, const uint32_t* __restrict__ codes, float* gin, int64_t n, TableArgs tab) {
+__device__ inline void bwd32_tile(const float* g, const uint32_t* codes, float* gin, int64_t n, const TableArgs& tab) {
   constexpr int kWords = Codes32<BITS>::kWords;
   constexpr uint32_t kMask = (1u << BITS) - 1u;
   const int lane = static_cast<int>(threadIdx.x & (kWave - 1));
@@ -1456,6 +1475,18 @@ __global__ __launch_bounds__(kThreads32) void bwd32_kernel(
       OutElements<P>(gin + t * kTile, rest * 4u).st4(element32(lane, i) * 4u, __float_as_uint(__uint_as_float(p[i]) * v));
     }
   }
+}
+
+template <int BITS, int P>
+__global__ __launch_bounds__(kThreads32) void bwd32_kernel(
+    const float* g, const uint32_t* __restrict__ codes, float* gin, int64_t n, TableArgs tab) {
+  bwd32_tile<BITS, P>(g, codes, gin, n, tab);
+}
+
+template <int BITS>
+__global__ __launch_bounds__(kThreads32) void bwd32_small_kernel(
+    TableArgs tab, const float* g, const uint32_t* __restrict__ codes, float* gin, int64_t n) {
+  bwd32_tile<BITS, kNt>(g, codes, gin, n, tab);
 }
 
 // ---------------------------------------------------------------- host side
@@ -1564,6 +1595,14 @@ bool store_nt(int64_t bytes) { return bytes >= kNtFrom && bytes < kNtUpto; }
 // 3-bit pass of 2^28 359.7 us, with nt 344.3; fp32 Sigmoid 4-bit of 2^26 177.2,
 // 173.8; the fp32 backward alone of 35M 45.4, 44.6).
 constexpr int64_t kGradThroughUpto = int64_t{1} << 27;
+
+// fp32 launches that run the small kernels: nothing preloaded, stores nt, the
+// boundaries put in place before the stream loads.  With fewer than four
+// workgroups the dispatcher's fetch of the preloaded arguments is on the only
+// path there is (12 ReLU layers of 6144 elements, 2 bits, with their backwards
+// in a graph: 48.2 us preloaded, 45.9 not; Tanh 4 bits 54.4 and 53.2); from the
+// fourth on the waves start sooner for it (8192 elements: 48.0 and 48.9).
+bool small32(int64_t n) { return n <= 3 * (kThreads32 / kWave) * kTile; }
 
 struct Launch {
   const fewbit_table* t;
@@ -1690,6 +1729,9 @@ hipError_t launch_fwd(const Launch& L) {
   const int64_t nw = fewbit_packed_words(L.n, BITS);
   const int sym = (L.t->flags & FEWBIT_FLAG_SYMMETRIC) ? 1 : 0;
   if constexpr (DT == FEWBIT_F32) {
+    if (small32(L.n))
+      return launch(fwd32_small_kernel<BITS, ACT>, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
+                    table_args(L.t), static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n, sym);
     auto kernel = store_nt(4 * L.n) ? fwd32_kernel<BITS, ACT, kNt> : fwd32_kernel<BITS, ACT, kThroughNt>;
     return launch(kernel, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
                   static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n, sym,
@@ -1753,6 +1795,9 @@ hipError_t launch_fwd_bits(const Launch& L) {
 template <int DT, int BITS>
 hipError_t launch_bwd(const Launch& L) {
   if constexpr (DT == FEWBIT_F32) {
+    if (small32(L.n))
+      return launch(bwd32_small_kernel<BITS>, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
+                    table_args(L.t), static_cast<const float*>(L.in), L.codes, static_cast<float*>(L.out), L.n);
     auto kernel = store_nt(4 * L.n)             ? bwd32_kernel<BITS, kNt>
                   : 4 * L.n <= kGradThroughUpto ? bwd32_kernel<BITS, kThrough>
                                                 : bwd32_kernel<BITS, kThroughNt>;

@@ -55,6 +55,14 @@ def test_partial_tile(bits, dt, rest):
             check_guarded(f"gelu_bf16_lm_ffn_16x2048x8192/b{bits}", dt, n, P.FLAG_TABLE_FWD)
 
 
+# both sides of the fp32 small kernels' limit (12 tiles)
+@pytest.mark.parametrize("key", ["gelu3_f32_1m/b3", "sigmoid4_f32_odd_67108863/b4", "sigmoid4_f32_odd_67108863/b4/sym",
+                                 "gelu_bf16_lm_ffn_16x2048x8192/b1", "silu2_f16_resnet_64x256x56x56/b2"])
+def test_short_fp32_launches(key):
+    for n in (1, 511, 512, 2048, 2049, 6143, 6144, 6145):
+        check_guarded(key, "f32", n)
+
+
 def _stack(table, n, dt, layers):
     """A graph of the forwards and then the backwards of `layers` layers."""
     sets = []
