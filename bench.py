@@ -71,13 +71,18 @@ def kernel_source_hash() -> str:
 
 def kernel_name(kind: str, dtype: str, bits: int, act: str, n: int, table_min: int) -> str:
     """Name of the library kernel a pass runs, as the rocprofv3 summaries
-    print it."""
+    print it (for tables whose boundaries are 0 or of ordinary size, as every
+    fitted one's are).  table_min: fewbit_fwd16_table_min, or 0 / 2^63 - 1
+    where the table / per-element kernel is forced."""
+    small = "_small" if dtype == "f32" and n <= 12 * 512 else ""
     if kind == "bwd":
-        return f"bwd32_kernel<f32,{bits}>" if dtype == "f32" else f"bwd_kernel<{dtype},{bits}>"
+        return f"bwd32{small}_kernel<f32,{bits}>" if dtype == "f32" else f"bwd_kernel<{dtype},{bits}>"
     if dtype == "f32":
-        return f"fwd32_kernel<f32,{bits},{act}>"
+        return f"fwd32{small}_kernel<f32,{bits},{act}>"
     table = "fwd16full_kernel" if dtype == "f16" else "fwd16_kernel"
-    k = table if n >= table_min else "fwd16v_kernel"
+    # at 3 and 4 bits bf16 uses its table below that count too
+    band = dtype == "bf16" and bits >= 3 and table_min < 2 ** 63 - 1 and 3 << 20 <= n <= 8 << 20
+    k = table if n >= table_min or band else "fwd16v_kernel"
     return f"{k}<{dtype},{bits},{act}>"
 
 

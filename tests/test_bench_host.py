@@ -133,3 +133,29 @@ def test_forced_forward_kernel_choice():
         tm = bench.forced_min(P, w, 3, choice)
         assert bench.kernel_name("fwd", "bf16", 3, "gelu", 1, tm).startswith(kernel + "<")
         assert bench.kernel_name("fwd", "bf16", 3, "gelu", w.n, tm).startswith(kernel + "<")
+
+
+def test_kernel_name_follows_the_dispatch_by_size():
+    # bf16 at 3 and 4 bits runs its table kernel from 3 to 8 Mi elements as
+    # well as from fewbit_fwd16_table_min on; fp32 has kernels for up to 12
+    # tiles.  The launches of the library decide (fewbit.hip: tab_by_size,
+    # small32); the limits are read from there.
+    import re
+    import paper_2202_00441_amd as P
+    with open(os.path.join(ROOT, "paper_2202_00441_amd", "csrc", "fewbit.hip")) as fh:
+        src = fh.read()
+    lo, hi = re.search(r"bits >= 3 && n >= int64_t\{(\d+)\} << 20 && n <= int64_t\{(\d+)\} << 20", src).groups()
+    lo, hi = int(lo) << 20, int(hi) << 20
+    tm = P.fwd16_table_min("sigmoid", 3, "bf16")
+    assert hi < tm
+    for n, k in ((lo - 1, "fwd16v"), (lo, "fwd16"), (hi, "fwd16"), (hi + 1, "fwd16v"), (tm, "fwd16")):
+        assert bench.kernel_name("fwd", "bf16", 3, "sigmoid", n, tm) == f"{k}_kernel<bf16,3,sigmoid>", n
+    assert bench.kernel_name("fwd", "bf16", 3, "sigmoid", lo, bench.forced_min(P, None, 3, "element")).startswith("fwd16v_")
+    assert bench.kernel_name("fwd", "f16", 3, "silu", lo, P.fwd16_table_min("silu", 3, "f16")).startswith("fwd16v_")
+    waves, tiles = re.search(r"small32\(int64_t n\) \{ return n <= (\d+) \* \(kThreads(\d+) / kWave\) \* kTile", src).groups()
+    assert (waves, tiles) == ("3", "32") and re.search(r"kThreads32 = 256;", src)
+    limit = 3 * (256 // 64) * 512
+    assert bench.kernel_name("fwd", "f32", 3, "gelu", limit, 0) == "fwd32_small_kernel<f32,3,gelu>"
+    assert bench.kernel_name("bwd", "f32", 3, "gelu", limit + 1, 0) == "bwd32_kernel<f32,3>"
+    assert bench._kernel_key("void (anonymous namespace)::fwd32_small_kernel<3, 0>(...)") == "fwd32_small_kernel<f32,3,gelu>"
+    assert bench._kernel_key("void (anonymous namespace)::bwd32_small_kernel<3>(...)") == "bwd32_small_kernel<f32,3>"
