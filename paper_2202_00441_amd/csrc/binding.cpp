@@ -16,6 +16,7 @@
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/dynamo/compiled_autograd.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/csrc/utils/object_ptr.h>
 #include <torch/csrc/utils/pybind.h>
@@ -30,6 +31,8 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <string>
+#include <vector>
 
 #include "fewbit.h"
 
@@ -191,6 +194,55 @@ PyObject* bwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   throw e;
 }
 
+// The gradient of one call of the layer.
+at::Tensor layer_grad(const fewbit_table& t, const at::Tensor& grad, const at::Tensor& codes) {
+  const at::Tensor g = grad.contiguous();
+  if (plain_mode() && plain(g) && storage_type(g) >= 0 && plain(codes) && codes.is_contiguous() &&
+      codes_fit(codes, g, t.bits)) {
+    at::AutoDispatchBelowADInplaceOrView below;
+    const c10::DeviceGuard guard(g.device());
+    at::Tensor gin = at::empty_like(g);
+    const int rc = run_bwd(t, g, codes, gin);
+    if (rc == FEWBIT_OK) return gin;
+    pybind11::gil_scoped_acquire gil;
+    if (PyObject* e = PyObject_CallFunction(error_class, "is", rc, "fewbit_bwd")) {
+      PyErr_SetObject(error_class, e);
+      Py_DECREF(e);
+    }
+    throw_python();
+  }
+  // codes that a hook has moved or replaced, a gradient of another kind
+  pybind11::gil_scoped_acquire gil;
+  THPObjectPtr og(THPVariable_Wrap(g)), oc(THPVariable_Wrap(codes));
+  THPObjectPtr ot(PyBytes_FromStringAndSize(reinterpret_cast<const char*>(&t), sizeof t));
+  if (!og || !oc || !ot) throw_python();
+  THPObjectPtr r(PyObject_CallFunctionObjArgs(general_bwd, ot.get(), og.get(), oc.get(), nullptr));
+  if (!r) throw_python();
+  return THPVariable_Unpack(r.get());
+}
+
+// The table's bytes as text ('a' .. 'p', two letters a byte) and back:
+// compiled autograd takes a call's constants as values of its own types.
+std::string text_of(const fewbit_table& t) {
+  const auto* b = reinterpret_cast<const unsigned char*>(&t);
+  std::string s;
+  s.reserve(2 * sizeof t);
+  for (size_t i = 0; i < sizeof t; ++i) {
+    s += static_cast<char>('a' + (b[i] >> 4));
+    s += static_cast<char>('a' + (b[i] & 15));
+  }
+  return s;
+}
+
+fewbit_table table_of_text(const std::string& s) {
+  fewbit_table t;
+  TORCH_CHECK(s.size() == 2 * sizeof t, "not a table");
+  auto* b = reinterpret_cast<unsigned char*>(&t);
+  for (size_t i = 0; i < sizeof t; ++i)
+    b[i] = static_cast<unsigned char>(((s[2 * i] - 'a') << 4) | (s[2 * i + 1] - 'a'));
+  return t;
+}
+
 // The layer's node: saves the packed codes alone (saved-tensor hooks see them)
 // and a copy of the table.
 struct FewBitNode : public torch::autograd::Node {
@@ -210,30 +262,36 @@ struct FewBitNode : public torch::autograd::Node {
       codes = codes_.unpack();
     }
     if (!task_should_compute_output(0)) return {at::Tensor()};
-    at::Tensor g = grads[0].defined() ? grads[0] : input_metadata(0).zeros_like();
-    g = g.contiguous();
-    if (plain_mode() && plain(g) && storage_type(g) >= 0 && plain(codes) && codes.is_contiguous() &&
-        codes_fit(codes, g, table_.bits)) {
-      at::AutoDispatchBelowADInplaceOrView below;
-      const c10::DeviceGuard guard(g.device());
-      at::Tensor gin = at::empty_like(g);
-      const int rc = run_bwd(table_, g, codes, gin);
-      if (rc == FEWBIT_OK) return {gin};
-      pybind11::gil_scoped_acquire gil;
-      if (PyObject* e = PyObject_CallFunction(error_class, "is", rc, "fewbit_bwd")) {
-        PyErr_SetObject(error_class, e);
-        Py_DECREF(e);
-      }
-      throw_python();
-    }
-    // codes that a hook has moved or replaced, a gradient of another kind
-    pybind11::gil_scoped_acquire gil;
-    THPObjectPtr og(THPVariable_Wrap(g)), oc(THPVariable_Wrap(codes));
-    THPObjectPtr ot(PyBytes_FromStringAndSize(reinterpret_cast<const char*>(&table_), sizeof table_));
-    if (!og || !oc || !ot) throw_python();
-    THPObjectPtr r(PyObject_CallFunctionObjArgs(general_bwd, ot.get(), og.get(), oc.get(), nullptr));
-    if (!r) throw_python();
-    return {THPVariable_Unpack(r.get())};
+    return {layer_grad(table_, grads[0].defined() ? grads[0] : input_metadata(0).zeros_like(), codes)};
+  }
+
+  // Compiled autograd: the codes are an input of the compiled graph, the table
+  // one of its constants, and the gradient an opaque call in it (as a Python
+  // function's backward is), never traced through.
+  void compiled_args(torch::dynamo::autograd::CompiledNodeArgs& args) const override {
+    args.collect(codes_, /*is_output=*/false);
+    args.collect(text_of(table_));
+  }
+
+  variable_list apply_with_saved(const variable_list& grads, torch::dynamo::autograd::SwapSavedVariables& saved) override {
+    namespace ca = torch::dynamo::autograd;
+    using Outputs = std::vector<std::optional<torch::autograd::InputMetadata>>;
+    saved.before(codes_);
+    ca::PackedArgs args;
+    args.pack(codes_.unpack());
+    args.pack(text_of(table_));
+    const auto& compiler = ca::getPyCompilerInterface();
+    const std::string fn = compiler->bind_function(
+        saved.get_py_compiler(), name(),
+        [](const variable_list& g, const std::vector<c10::IValue>& a) -> variable_list {
+          if (!g[0].defined()) return {at::Tensor()};
+          return {layer_grad(table_of_text(a[1].toStringRef()), g[0], a[0].toTensor())};
+        },
+        {at::TensorType::get(), at::StringType::get()}, /*is_custom_function=*/true, /*is_traceable=*/false);
+    variable_list out = compiler->call_function(saved.get_py_compiler(), "apply_functional", fn, grads, args.vec(),
+                                                ca::IValuePacker<Outputs>::pack(ca::get_input_metadata(next_edges())));
+    saved.after(codes_);
+    return out;
   }
 };
 

@@ -193,3 +193,26 @@ def test_dispatch_and_function_modes_see_the_general_path():
         y2, c2 = P.fwd(LAYER.table, x)
     assert Count.ops > 0 and torch.equal(y, y2) and torch.equal(codes, c2)
     assert _lib._native.fwd(LAYER.table.c, x.cpu(), None, None) is None
+
+
+def test_compiled_autograd():
+    # two layers with tables of their own, saved-tensor hooks, and a second
+    # backward that reuses the compiled graph
+    from torch._dynamo import compiled_autograd
+    other = P.FewBitAct("silu", 2)
+    fs = [(LAYER, other), (_general, lambda t: P.FewBitActivation.apply(t, other.table))]
+    for seed in (1, 2):
+        grads = []
+        for f, g in fs:
+            for compiled in (False, True):
+                x = _x(3001, seed=seed).requires_grad_()
+                with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), lambda t: t.cuda()):
+                    y = g(f(x) * 2).sum() + f(x).float().square().sum()
+                if compiled:
+                    with compiled_autograd._enable(torch.compile(backend="eager")):
+                        y.backward()
+                else:
+                    y.backward()
+                grads.append(x.grad)
+        for g in grads[1:]:
+            _same(g, grads[0])
