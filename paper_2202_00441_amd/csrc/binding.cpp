@@ -14,6 +14,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
+#include <torch/csrc/autograd/python_cpp_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/dynamo/compiled_autograd.h>
@@ -32,6 +33,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <typeinfo>
 #include <vector>
 
 #include "fewbit.h"
@@ -250,19 +252,19 @@ struct FewBitNode : public torch::autograd::Node {
   fewbit_table table_;
 
   std::string name() const override { return "FewBitActivationBackward"; }
+  at::Tensor codes() {
+    std::lock_guard<std::mutex> lock(mutex_);
+    return codes_.unpack();
+  }
   void release_variables() override {
     std::lock_guard<std::mutex> lock(mutex_);
     codes_.reset_data();
   }
 
   variable_list apply(variable_list&& grads) override {
-    at::Tensor codes;
-    {
-      std::lock_guard<std::mutex> lock(mutex_);
-      codes = codes_.unpack();
-    }
+    const at::Tensor saved = codes();
     if (!task_should_compute_output(0)) return {at::Tensor()};
-    return {layer_grad(table_, grads[0].defined() ? grads[0] : input_metadata(0).zeros_like(), codes)};
+    return {layer_grad(table_, grads[0].defined() ? grads[0] : input_metadata(0).zeros_like(), saved)};
   }
 
   // Compiled autograd: the codes are an input of the compiled graph, the table
@@ -294,6 +296,26 @@ struct FewBitNode : public torch::autograd::Node {
     return out;
   }
 };
+
+// grad_fn.saved_tensors, as a Python function's has it
+PyObject* saved_tensors(PyObject* self, void*) {
+  HANDLE_TH_ERRORS
+  auto* node = static_cast<FewBitNode*>(reinterpret_cast<torch::autograd::THPCppFunction*>(self)->cdata.get());
+  at::Tensor codes;
+  {
+    pybind11::gil_scoped_release no_gil;
+    codes = node->codes();
+  }
+  THPObjectPtr oc(THPVariable_Wrap(codes));
+  return oc ? PyTuple_Pack(1, oc.get()) : nullptr;
+  END_HANDLE_TH_ERRORS
+}
+
+using namespace torch::autograd;      // the properties macro names its getters without it
+PyTypeObject node_type;
+PyGetSetDef node_properties[] = {THP_FUNCTION_DEFAULT_PROPERTIES,
+                                 {"saved_tensors", saved_tensors, nullptr, nullptr, nullptr},
+                                 {nullptr, nullptr, nullptr, nullptr, nullptr}};
 
 // activation(table, x) -> y with its history, a status, or None
 PyObject* activation(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
@@ -350,4 +372,10 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native(void) { return PyModule_Create(&module_def); }
+PyMODINIT_FUNC PyInit__native(void) {
+  HANDLE_TH_ERRORS
+  torch::autograd::_initFunctionPyTypeObject(node_type, "FewBitActivationBackward", node_properties, nullptr);
+  torch::autograd::registerCppFunction(typeid(FewBitNode), &node_type);
+  return PyModule_Create(&module_def);
+  END_HANDLE_TH_ERRORS
+}

@@ -216,3 +216,19 @@ def test_compiled_autograd():
                 grads.append(x.grad)
         for g in grads[1:]:
             _same(g, grads[0])
+
+
+def test_grad_fn_shows_the_saved_codes():
+    x = _x(1000).requires_grad_()
+    codes = P.fwd(LAYER.table, x.detach())[1]
+    for f in (LAYER, _general):
+        y = f(x)
+        assert y.grad_fn.name().startswith("FewBitActivation") and len(y.grad_fn.next_functions) == 1
+        (saved,) = y.grad_fn.saved_tensors
+        assert torch.equal(saved, codes)
+        seen = []
+        y.grad_fn.register_hook(lambda gi, go: seen.append((gi[0].shape, go[0].shape)))
+        y.sum().backward()
+        assert seen == [(x.shape, x.shape)]
+        with pytest.raises(RuntimeError, match="second time"):
+            y.grad_fn.saved_tensors
