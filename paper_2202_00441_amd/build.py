@@ -1,5 +1,7 @@
 """Build libfewbit.so (HIP kernels for gfx950 + host fit + C ABI) and _native.so
-(the calls on torch tensors, host code linked against it) in-tree.
+(the calls on torch tensors, host code linked against it) in-tree.  Where torch
+or its headers are missing only the first is built: it needs neither, and a
+program that uses include/fewbit.h needs no more.
 
     python -m paper_2202_00441_amd.build      # or: python paper_2202_00441_amd/build.py
 
@@ -38,8 +40,19 @@ CXX = os.environ.get("CXX", "g++")
 
 def build(verbose: bool = False, extra=()) -> str:
     _compile([HIPCC, *FLAGS, *extra, "-o", OUT + ".tmp", *SOURCES], OUT, verbose)
-    build_native(verbose)            # links libfewbit.so, so after it
+    if _torch_headers():
+        build_native(verbose)        # links libfewbit.so, so after it
+    else:
+        print("no torch with headers here: _native.so is not built, the Python package needs it")
     return OUT
+
+
+def _torch_headers() -> bool:
+    try:
+        import torch
+    except ImportError:
+        return False
+    return os.path.isdir(os.path.join(os.path.dirname(torch.__file__), "include", "torch", "csrc"))
 
 
 def build_native(verbose: bool = False) -> str:

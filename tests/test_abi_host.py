@@ -329,3 +329,19 @@ def test_single_hip_runtime_in_process():
             if "libamdhip64" in line:
                 paths.add(os.path.realpath(line.split()[-1]))
     assert len(paths) == 1, paths
+
+
+def test_the_library_builds_without_torch(monkeypatch, capsys):
+    import importlib.util
+    import sys
+    spec = importlib.util.spec_from_file_location("_fewbit_build_alone", os.path.join(ROOT, "paper_2202_00441_amd", "build.py"))
+    b = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(b)
+    built = []
+    monkeypatch.setattr(b, "_compile", lambda cmd, out, verbose: built.append(os.path.basename(out)))
+    b.build()
+    assert built == ["libfewbit.so", "_native.so"]
+    built.clear()
+    monkeypatch.setitem(sys.modules, "torch", None)          # `import torch` raises ImportError
+    b.build()
+    assert built == ["libfewbit.so"] and "_native.so is not built" in capsys.readouterr().out
