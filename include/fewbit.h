@@ -19,8 +19,9 @@
  *   - The caller owns every buffer.  The library never allocates or frees
  *     device memory and never synchronises the caller's streams.
  *   - All argument checks run on the host before anything is launched, so a
- *     call that returns an error has written nothing.  Asynchronous device
- *     faults surface at the caller's next synchronisation.
+ *     call that returns an error has written nothing (except beyond 2^34
+ *     elements, see fewbit_fwd).  Asynchronous device faults surface at the
+ *     caller's next synchronisation.
  *   - Global state: the compute-unit count of each device, read once (it
  *     sizes the launch grid).  The library keeps no device memory of its
  *     own: the fp16 / bf16 forward builds its lookup tables in every
@@ -173,6 +174,9 @@ int64_t fewbit_packed_words(int64_t n, int32_t bits);
  *          words; must not overlap x or y
  *   n      element count >= 0 (0 is a no-op)
  *   stream hipStream_t (as void*), the launch is asynchronous on it
+ *
+ * Beyond 2^34 elements fewbit_fwd and fewbit_bwd may take several launches;
+ * if a later one fails (FEWBIT_E_HIP), the earlier parts are still written.
  */
 int fewbit_fwd(const fewbit_table* t, int32_t dtype, const void* x, void* y,
                uint32_t* codes, int64_t n, void* stream);

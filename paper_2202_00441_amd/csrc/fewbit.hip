@@ -1558,11 +1558,22 @@ dim3 grid_for(int64_t n, int waves_per_block, int wg_per_cu, int unroll) {
 int64_t tiles_of(int64_t n) { return n / kTile + (n % kTile != 0); }
 
 // The grid of a launch with one pass per workgroup over `per` units of its
-// work.  (A launch holds at most 2^32 threads; what needs more is refused by
-// the runtime.)
-dim3 grid_of(int64_t units, int per) {
-  const int64_t blocks = (units + per - 1) / per;
-  return dim3(static_cast<unsigned>(blocks > INT32_MAX ? INT32_MAX : blocks));
+// work, at most a part's (in_parts).
+dim3 grid_of(int64_t units, int per) { return dim3(static_cast<unsigned>((units + per - 1) / per)); }
+
+// A launch holds fewer than 2^32 threads, and the kernels with one pass per
+// wave have 64 for 512 elements: longer tensors go in parts of whole tiles, and
+// of whole runs of the backward's tile order.  f(at, m) launches the m elements
+// from `at` on; their codes start at word at / 32 * bits.
+template <class F>
+hipError_t in_parts(int64_t n, F f) {
+  constexpr int64_t kPart = int64_t{1} << 34;
+  static_assert(kPart % (16 * kTile) == 0 && kPart / kTile * kWave < int64_t{1} << 32, "whole runs that fit a launch");
+  for (int64_t at = 0; at < n; at += kPart) {
+    const hipError_t e = f(at, n - at < kPart ? n - at : kPart);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // The stream must belong to the current device: the grid size, the output
@@ -1733,9 +1744,11 @@ hipError_t launch_fwd(const Launch& L) {
       return launch(fwd32_small_kernel<BITS, ACT>, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
                     table_args(L.t), static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n, sym);
     auto kernel = store_nt(4 * L.n) ? fwd32_kernel<BITS, ACT, kNt> : fwd32_kernel<BITS, ACT, kThroughNt>;
-    return launch(kernel, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
-                  static_cast<const float*>(L.in), static_cast<float*>(L.out), L.codes, L.n, sym,
-                  table_args(L.t));
+    return in_parts(L.n, [&](int64_t at, int64_t m) {
+      return launch(kernel, grid_of(tiles_of(m), kThreads32 / kWave), kThreads32, L.s,
+                    static_cast<const float*>(L.in) + at, static_cast<float*>(L.out) + at,
+                    L.codes + at / 32 * BITS, m, sym, table_args(L.t));
+    });
   } else {
     const bool holds = DT == FEWBIT_BF16 && L.n < kTabUpto && fwd16_out::holds(ACT, sym != 0, L.t->s, (1 << BITS) - 1);
     const bool by_size = holds ? tab_by_size(ACT, BITS, L.n) : L.n >= table_min_of(DT, ACT, BITS);
@@ -1745,17 +1758,10 @@ hipError_t launch_fwd(const Launch& L) {
       const bool nt = store_nt(2 * L.n);
       auto kernel = sym ? (nt ? fwd16v_kernel<DT, BITS, ACT, true, kNt> : fwd16v_kernel<DT, BITS, ACT, true, kThroughNt>)
                         : (nt ? fwd16v_kernel<DT, BITS, ACT, false, kNt> : fwd16v_kernel<DT, BITS, ACT, false, kThroughNt>);
-      // a launch holds fewer than 2^32 threads, 64 per tile of 512: longer
-      // tensors go in parts of whole tiles
-      constexpr int64_t kPart = int64_t{1} << 34;
-      for (int64_t at = 0; at < L.n; at += kPart) {
-        const int64_t m = L.n - at < kPart ? L.n - at : kPart;
-        const hipError_t e = launch(kernel, grid_of(tiles_of(m), 1), kWave, L.s,
-                                    static_cast<const uint16_t*>(L.in) + at, static_cast<uint16_t*>(L.out) + at,
-                                    L.codes + at / 32 * BITS, m, table_args(L.t));
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
+      return in_parts(L.n, [&](int64_t at, int64_t m) {
+        return launch(kernel, grid_of(tiles_of(m), 1), kWave, L.s, static_cast<const uint16_t*>(L.in) + at,
+                      static_cast<uint16_t*>(L.out) + at, L.codes + at / 32 * BITS, m, table_args(L.t));
+      });
     }
     if constexpr (DT == FEWBIT_BF16) {
       if (holds)
@@ -1801,21 +1807,25 @@ hipError_t launch_bwd(const Launch& L) {
     auto kernel = store_nt(4 * L.n)             ? bwd32_kernel<BITS, kNt>
                   : 4 * L.n <= kGradThroughUpto ? bwd32_kernel<BITS, kThrough>
                                                 : bwd32_kernel<BITS, kThroughNt>;
-    return launch(kernel, grid_of(tiles_of(L.n), kThreads32 / kWave), kThreads32, L.s,
-                  static_cast<const float*>(L.in), L.codes, static_cast<float*>(L.out), L.n,
-                  table_args(L.t));
+    return in_parts(L.n, [&](int64_t at, int64_t m) {
+      return launch(kernel, grid_of(tiles_of(m), kThreads32 / kWave), kThreads32, L.s,
+                    static_cast<const float*>(L.in) + at, L.codes + at / 32 * BITS,
+                    static_cast<float*>(L.out) + at, m, table_args(L.t));
+    });
   } else {
-    // one-wave workgroups: a whole number of runs of the tile order over the
-    // full tiles, and up to the partial tile's unit when that lies past them
-    const int64_t full = L.n / kTile, run = BwdOrder<BITS>::kRun;
-    int64_t units = (full + run - 1) / run * run;
-    if (L.n % kTile != 0 && units <= BwdOrder<BITS>::unit_of_tile(full)) units = BwdOrder<BITS>::unit_of_tile(full) + 1;
     auto kernel = store_nt(2 * L.n)             ? bwd_kernel<DT, BITS, kNt>
                   : 2 * L.n <= kGradThroughUpto ? bwd_kernel<DT, BITS, kThrough>
                                                 : bwd_kernel<DT, BITS, kThroughNt>;
-    return launch(kernel, grid_of(units, 1), kWave, L.s,
-                  static_cast<const uint16_t*>(L.in), L.codes, static_cast<uint16_t*>(L.out), L.n,
-                  table_args(L.t));
+    return in_parts(L.n, [&](int64_t at, int64_t m) {
+      // one-wave workgroups: a whole number of runs of the tile order over the
+      // full tiles, and up to the partial tile's unit when that lies past them
+      using Order = BwdOrder<BITS>;
+      const int64_t full = m / kTile;
+      int64_t units = (full + Order::kRun - 1) / Order::kRun * Order::kRun;
+      if (m % kTile != 0 && units <= Order::unit_of_tile(full)) units = Order::unit_of_tile(full) + 1;
+      return launch(kernel, grid_of(units, 1), kWave, L.s, static_cast<const uint16_t*>(L.in) + at,
+                    L.codes + at / 32 * BITS, static_cast<uint16_t*>(L.out) + at, m, table_args(L.t));
+    });
   }
 }
 

@@ -98,3 +98,47 @@ def test_forward_in_parts():
     check_exact(got.astype(np.int64), np.asarray(idx_ref).astype(np.int64), "codes sampled")
     del x, codes
     torch.cuda.empty_cache()
+
+
+@pytest.mark.slow
+@pytest.mark.parametrize("dt,bits", [("bf16", 3), ("f32", 1)])
+def test_both_directions_in_parts(dt, bits):
+    # past 2^35 elements every direction needs several launches (one holds fewer
+    # than 2^32 threads, 64 for 512 elements): the forward and then the backward,
+    # each in place (up to 142 GB resident), checked around the parts' seams, at
+    # the end and at random
+    n, part = (1 << 35) + 12345, 1 << 34
+    s = [0.25] if bits == 1 else [-1.5, -1.0, -0.5, 0.0, 0.5, 1.0, 1.5]
+    v = [0.25 * (m + 1) for m in range(1 << bits)]
+    table = P.Table.from_values(P.ACTS["relu"], bits, s, v)
+    kind, size = (torch.int32, np.uint32) if dt == "f32" else (torch.int16, np.uint16)
+    tdt, odt = (torch.float32, O.F32) if dt == "f32" else (torch.bfloat16, O.BF16)
+    print(f"[parts] {dt} n={n} bits={bits}", flush=True)
+    x = torch.empty(n, dtype=tdt, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for at in range(0, n, 1 << 30):
+        x[at:at + (1 << 30)].normal_(generator=gen)
+    rng = np.random.default_rng(6)
+    idx = np.unique(np.concatenate([np.arange(k * part - 2048, k * part + 2048) for k in (1, 2)] +
+                                   [np.arange(n - 3000, n), np.arange(2048), rng.integers(0, n, 100000)]))
+    it = torch.from_numpy(idx).cuda()
+    sample = lambda: x[it].view(kind).cpu().numpy().view(size)  # noqa: E731
+    xs = sample()
+    _, codes = P.fwd(table, x, y=x)
+    ys = sample()
+    y_ref, _, idx_ref = O.fwd(OACT["relu"], odt, bits, np.float32(s), xs, want_idx=True)
+    idx_ref = np.asarray(idx_ref).astype(np.int64)
+    check_y(ys, y_ref, dt, "y sampled")
+    got = np.zeros(idx.size, np.int64)
+    for b in range(bits):                       # a code may lie across two words
+        at = bits * idx + b
+        words = codes[torch.from_numpy(at // 32).cuda()].cpu().numpy().view(np.uint32)
+        got |= ((words >> (at % 32).astype(np.uint32)) & 1).astype(np.int64) << b
+    check_exact(got, idx_ref, "codes sampled")
+    P.bwd(table, x, codes, grad_in=x)
+    y32 = ys.view(np.float32) if dt == "f32" else (ys.astype(np.uint32) << 16).view(np.float32)
+    want = y32 * np.float32(v)[idx_ref]
+    want = want.view(np.uint32) if dt == "f32" else O.round_array(O.BF16, want.astype(np.float64))
+    check_exact(sample(), want, "grad_in sampled")
+    del x, codes
+    torch.cuda.empty_cache()
