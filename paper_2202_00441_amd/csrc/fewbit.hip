@@ -1535,24 +1535,13 @@ int device_cus() {
   return c;
 }
 
-// Workgroups for n elements when each has `waves_per_block` streaming waves
-// that take `unroll` tiles per loop trip: one tile group per wave at most,
-// capped at wg_per_cu per compute unit when wg_per_cu > 0, and at 2^30
-// workgroups in any case (beyond 2^42 or so elements, far more than device
-// memory holds); every kernel's waves walk the tile groups, so a capped grid
-// still covers all of them.
-dim3 grid_for(int64_t n, int waves_per_block, int wg_per_cu, int unroll) {
-  constexpr int64_t kMaxBlocks = int64_t{1} << 30;
-  const int64_t tiles = n / kTile + (n % kTile != 0);
-  const int64_t groups = (tiles + unroll - 1) / unroll;
-  int64_t blocks = (groups + waves_per_block - 1) / waves_per_block;
-  if (wg_per_cu > 0) {
-    const int64_t cap = static_cast<int64_t>(device_cus()) * wg_per_cu;
-    if (blocks > cap) blocks = cap;
-  }
-  if (blocks > kMaxBlocks) blocks = kMaxBlocks;
-  if (blocks < 1) blocks = 1;
-  return dim3(static_cast<unsigned>(blocks));
+// Workgroups of the full-range table kernel, whose waves walk the tiles in
+// groups: one group per wave at most, and at most what the chip holds at once.
+dim3 persistent_grid(int64_t n) {
+  constexpr int64_t kPerBlock = static_cast<int64_t>(FEWBIT_FWD16_THREADS / kWave) * FEWBIT_FWD16_UNROLL * kTile;
+  const int64_t blocks = n / kPerBlock + (n % kPerBlock != 0);
+  const int64_t cap = static_cast<int64_t>(device_cus()) * FEWBIT_FWD16_WG_PER_CU;
+  return dim3(static_cast<unsigned>(blocks < cap ? blocks : cap));
 }
 
 int64_t tiles_of(int64_t n) { return n / kTile + (n % kTile != 0); }
@@ -1768,8 +1757,7 @@ hipError_t launch_fwd(const Launch& L) {
         return L.n < kTabLargeFrom ? launch_tab<DT, BITS, ACT, 1024, 0>(L, nw, sym)
                                    : launch_tab<DT, BITS, ACT, 512, 4>(L, nw, sym);
     }
-    const dim3 grid = grid_for(L.n, FEWBIT_FWD16_THREADS / kWave, FEWBIT_FWD16_WG_PER_CU, FEWBIT_FWD16_UNROLL);
-    return launch(fwd16full_kernel<DT, BITS, ACT>, grid, FEWBIT_FWD16_THREADS, L.s,
+    return launch(fwd16full_kernel<DT, BITS, ACT>, persistent_grid(L.n), FEWBIT_FWD16_THREADS, L.s,
                   static_cast<const uint16_t*>(L.in), static_cast<uint16_t*>(L.out), L.codes, L.n, nw,
                   table_args(L.t), sym, out_runs<DT, ACT>());
   }
