@@ -164,17 +164,32 @@ def test_checkpoint(reentrant):
 
 
 def test_backward_runs_on_the_forwards_stream():
+    # the forward waits on its stream behind a delay, in memory that held other
+    # bytes before: a backward on any other stream would read those
     side = torch.cuda.Stream()
     x = _x(1 << 20).requires_grad_()
-    (ref,) = torch.autograd.grad(_general(x), x, torch.ones_like(x))
+    ones = torch.ones_like(x)
+    (ref,) = torch.autograd.grad(_general(x), x, ones)
     side.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(side):
-        y = LAYER(x)
-        g = torch.ones_like(y)
-    (got,) = torch.autograd.grad(y, x, g)
-    torch.cuda.current_stream().wait_stream(side)
-    torch.cuda.synchronize()
-    _same(got, ref)
+    for delay in (0, 20_000_000):                  # the first pass loads and allocates
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            stale = [torch.full((P.packed_words(x.numel(), 3),), 0x2D2D2D2D, dtype=torch.int32, device="cuda")
+                     for _ in range(2)]
+            stale += [torch.full_like(x, -3.0) for _ in range(3)]
+            where = {t.data_ptr() for t in stale}
+            del stale
+            torch.cuda._sleep(delay)
+            y = LAYER(x)
+            g = torch.ones_like(y)
+        (codes,) = y.grad_fn.saved_tensors
+        assert codes.data_ptr() in where and g.data_ptr() in where
+        (got,) = torch.autograd.grad(y, x, g)
+        busy = not side.query()
+        torch.cuda.synchronize()
+        _same(got, ref)
+        del y, g, codes, got
+    assert busy, "the delay was over before the backward was launched"
 
 
 def test_dispatch_and_function_modes_see_the_general_path():

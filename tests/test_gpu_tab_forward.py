@@ -1,6 +1,7 @@
 """The bf16 table forward at the sizes where its tiling can go wrong, and with
-boundaries at the edges of what its table holds, against the oracle: codes
-and grad_in bit-exact, y within one unit in the last place.  Sizes: one
+boundaries at the edges of what its table holds, and the full-range kernel
+with boundaries that table does not hold, against the oracle: codes bit-exact,
+y within one unit in the last place.  Sizes: one
 element, both sides of a tile and of a workgroup's 32 tiles (or 8
 workgroups' 16), and both sides of the size where the launch shape changes."""
 import numpy as np
@@ -72,6 +73,24 @@ def test_boundaries_at_the_edges(act, symmetric):
     for s in sets:
         _check(act, 1, s, [0.25, 0.75], pats, symmetric, label=f"s={s}")
     _check(act, 2, [-1.5, 0.0, 1.5], [0.0, 0.25, 0.5, 1.0], pats, symmetric, label="around 0")
+
+
+# the last size: 4096 groups of 4 tiles, two for each of the grid's waves on 256
+# compute units, two leftover tiles and a partial one
+@pytest.mark.parametrize("n", [1, 511, 513, 2 * 65536 + 77, (1 << 23) + 1234])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_full_range_kernel(bits, symmetric, n):
+    s, v = _levels(bits)
+    x = np.random.default_rng(n + bits).integers(0, 1 << 16, n).astype(np.uint16)      # every kind of pattern
+    act = ("gelu", "softplus", "tanh")[bits - 2]
+    if symmetric:
+        s = [abs(s[0]) / len(s) * (m + 1) for m in range(len(s))]
+    tiny = sorted([1e-39] + [b for b in s if abs(b) > 1e-3])[:len(s)]
+    huge = sorted(s[1:] + [3e38])
+    for held_out in (tiny, huge):
+        held_out = held_out + [4.0 + m for m in range(len(s) - len(held_out))]
+        _check(act, bits, held_out, v, x, symmetric, label=f"not held, n={n}")
 
 
 @pytest.mark.slow
