@@ -189,8 +189,8 @@ int fewbit_fwd(const fewbit_table* t, int32_t dtype, const void* x, void* y,
  * type (dtype FEWBIT_F16 or FEWBIT_BF16); INT64_MAX for the per-element
  * kernel at every size.  Below the count, bf16 forwards of 3 to 8 Mi
  * elements use the table kernel too at 3 and 4 bits.  The count of bf16 is
- * that of tables whose boundaries are 0 or of ordinary size (2^-9 to 15 in
- * magnitude); others switch at larger sizes.  All kernels give results
+ * that of tables whose boundaries are 0 or of ordinary size (magnitudes
+ * above 2^-9 and below 15); others switch at larger sizes or never.  All kernels give results
  * within the same bounds: indices and codes identical, y within one unit in
  * the last place of the correctly rounded f.  This only tells a caller (or
  * a test) which kernel a given n reaches.  Returns -1 for an unknown

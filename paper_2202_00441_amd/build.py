@@ -10,7 +10,8 @@ Flags:
   -O3, no fast-math             IEEE fp32 semantics, denormals kept
   -packed-fp32-ops disabled     no packed fp32 VALU forms are generated
   kernarg preload               pointers and size arrive in scalar registers with the wave:
-                                its first loads wait for no load of their addresses
+                                its first loads wait for no load of their addresses (leading
+                                pointers and integers only; none if a structure comes first)
   constexpr steps               the bf16 output factors are evaluated at compile time
 """
 import os

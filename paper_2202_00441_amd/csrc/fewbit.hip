@@ -95,7 +95,8 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 //
 // Cache-policy bits: 2 = nt (streaming, not kept in cache), 16 = sc1 (device
 // scope: a store is written through the L2).  Loads are nt.  Stores are nt
-// alone, or through, or both, by the size of the tensor (store_nt).
+// alone, or through, or both, by the size of the tensor (store_nt); the two
+// table forwards store both ways at every size (launch_tab).
 constexpr int kNt = 2, kThrough = 16, kThroughNt = 18;
 
 struct Span {
@@ -1579,16 +1580,24 @@ int check_stream_device(hipStream_t stream) {
 // Its lines then stay dirty in the 32 MB of L2 and are written back when the
 // kernel ends, with nothing left to overlap with: writing through is faster on
 // small tensors (a graph of 12 bf16 GELU layers of 2^17 elements, 24 kernels:
-// 63.5 -> 56.7 us) and on large ones (16-bit backward of 2^28 elements, 3
+// 56.7 -> 52.6 us) and on large ones (16-bit backward of 2^28 elements, 3
 // bits: 181.4 -> 175.5 us; fp16 SiLU 2-bit pass of 51.4M: 71.1 -> 67.1; fp32
-// Tanh 3-bit pass of 2^25: 90.4 -> 84.4).  From 1 MiB up to 16, where a stack of
-// layers fits the 256 MB memory-side cache but not the L2, nt alone is (12 fp16
-// SiLU layers of 2^20: 69.8 and 73.7 us).  y is stored nt as well as through
+// Tanh 3-bit pass of 2^25: 90.4 -> 84.4).  Between, what decides is not this
+// tensor but what is live around it, which a launch does not know: whether a
+// stack fits the 256 MB memory-side cache but not the L2.  nt alone stands for
+// the stack of many layers.  In a graph, nt and through: 12 fp16 SiLU layers of
+// 2^21 elements 82.8 and 89.0 us, 12 fp32 Tanh (3 bits) 107.7 and 112.3; but 4
+// layers of 2^19 23.2 and 22.0 and 24.3 and 23.0, 12 of 2^19 54.1 and 51.3 and
+// 65.2 and 62.5, 12 SiLU of 6 * 2^20 153 and 147.  y is stored nt as well as through
 // (its forward with through alone: 71.3 and 88.5 us on the two passes above),
 // a short gradient is not (4.97 against 5.08 us at 2^22).
 constexpr int64_t kNtFrom = int64_t{1} << 20, kNtUpto = int64_t{1} << 24;
 bool store_nt(int64_t bytes) { return bytes >= kNtFrom && bytes < kNtUpto; }
 
+// (A forward or a backward repeated alone on the same buffers is another matter:
+// fp32 1-bit forward of 22M 26.5 us with nt, 28.1 as it is; fp32 4-bit backward
+// of 2^26 87.2 and 88.5.  Over changing buffers the two are level.)
+//
 // The gradient up to here is left in the memory-side cache for its reader
 // (fp32 Tanh 3-bit pass of 2^25 elements 85.1 us, with nt 87.8); a longer one
 // does not stay there, and with nt it takes no room from what does (bf16 GELU
@@ -1695,8 +1704,8 @@ bool tab_by_size(int act, int bits, int64_t n) {
 // 11.5 and 12.9 us, 2^25 27.0 and 26.8, 2^28 191 and 186.
 constexpr int64_t kTabLargeFrom = int64_t{1} << 25;
 
-// Its launches hold 2^32 threads of 16 elements; the full-range kernel's grid
-// does not grow with the tensor.
+// A launch of it holds fewer than 2^32 threads of 16 elements, so 2^35 elements
+// fit with room; the full-range kernel's grid does not grow with the tensor.
 constexpr int64_t kTabUpto = int64_t{1} << 35;
 
 // A launch by the runtime's own call, which returns its status: the <<<>>> form
@@ -1714,6 +1723,11 @@ hipError_t launch(void (*kernel)(P...), dim3 grid, unsigned threads, hipStream_t
   return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(threads), pointers, 0, stream);
 }
 
+// It stores nt and through at every size, also where the other kernels store nt
+// alone (3 to 8 Mi elements), for the stacks' sake.  Graphs of 12 GELU layers,
+// 3 bits, against nt alone: 4 Mi 128.9 and 135.1 us, 8 Mi 180.8 and 182.6; one
+// ReLU 4-bit pass of 6 Mi 11.5 and 11.8, of 8 Mi 13.0 and 12.5.  (The full-range
+// kernel is chosen only at sizes where the others do the same.)
 template <int DT, int BITS, int ACT, int THREADS, int RUN>
 hipError_t launch_tab(const Launch& L, int64_t nw, int sym) {
   // elements of a workgroup, or of the 8 that share runs of tiles

@@ -36,7 +36,9 @@ constexpr double two_to(int e) {          // -1022 <= e <= 1023
   return __builtin_bit_cast(double, static_cast<uint64_t>(1023 + e) << 52);
 }
 
-// e^x for -600 < x <= 0: Taylor series of the remainder of ln 2
+// e^x for -600 < x <= 0: Taylor series of the remainder of ln 2, which is
+// subtracted in two parts (the split of fdlibm's e_exp.c: the first has trailing
+// zeros, so its multiple is exact)
 constexpr double exp_of(double x) {
   const int k = static_cast<int>(x * 1.4426950408889634074 - 0.5);
   const double r = (x - k * 0.693147180369123816490) - k * 1.90821492927058770002e-10;
