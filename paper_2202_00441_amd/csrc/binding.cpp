@@ -24,7 +24,9 @@
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/SequenceNumber.h>
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
+#include <ATen/record_function.h>
 #include <c10/core/DeviceGuard.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
@@ -328,7 +330,9 @@ PyObject* activation(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   int rc;
   {
     pybind11::gil_scoped_release no_gil;
-    const c10::DeviceGuard guard(x->device());
+    // the profiler's range of the call, as a Python function has it
+    RECORD_FUNCTION("FewBitActivation", std::vector<c10::IValue>{*x}, static_cast<int64_t>(at::sequence_number::peek()));
+    const c10::DeviceGuard device(x->device());
     at::Tensor codes;
     {
       at::AutoDispatchBelowADInplaceOrView below;

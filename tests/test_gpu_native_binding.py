@@ -247,3 +247,14 @@ def test_grad_fn_shows_the_saved_codes():
         assert seen == [(x.shape, x.shape)]
         with pytest.raises(RuntimeError, match="second time"):
             y.grad_fn.saved_tensors
+
+
+def test_the_profiler_sees_the_layer():
+    x = _x(1000).requires_grad_()
+    for f in (LAYER, _general):
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU], record_shapes=True) as p:
+            f(x).sum().backward()
+        shapes = {e.name: e.input_shapes for e in p.events()}
+        assert shapes["FewBitActivation"][0] == [1000] and "FewBitActivationBackward" in shapes
+        seq = {e.name: e.sequence_nr for e in p.events()}
+        assert seq["FewBitActivation"] == seq["FewBitActivationBackward"] >= 0
