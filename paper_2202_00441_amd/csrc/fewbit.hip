@@ -1554,11 +1554,13 @@ dim3 grid_of(int64_t units, int per) { return dim3(static_cast<unsigned>((units 
 // A launch holds fewer than 2^32 threads, and the kernels with one pass per
 // wave have 64 for 512 elements: longer tensors go in parts of whole tiles, and
 // of whole runs of the backward's tile order.  f(at, m) launches the m elements
-// from `at` on; their codes start at word at / 32 * bits.
+// from `at` on; their codes start at word at / 32 * bits.  A size that no device
+// memory holds (half a terabyte from 2^38 elements on) launches nothing.
 template <class F>
 hipError_t in_parts(int64_t n, F f) {
   constexpr int64_t kPart = int64_t{1} << 34;
   static_assert(kPart % (16 * kTile) == 0 && kPart / kTile * kWave < int64_t{1} << 32, "whole runs that fit a launch");
+  if (n >= int64_t{1} << 38) return hipErrorInvalidConfiguration;
   for (int64_t at = 0; at < n; at += kPart) {
     const hipError_t e = f(at, n - at < kPart ? n - at : kPart);
     if (e != hipSuccess) return e;
@@ -1588,9 +1590,11 @@ int check_stream_device(hipStream_t stream) {
 // the stack of many layers.  In a graph, nt and through: 12 fp16 SiLU layers of
 // 2^21 elements 82.8 and 89.0 us, 12 fp32 Tanh (3 bits) 107.7 and 112.3; but 4
 // layers of 2^19 23.2 and 22.0 and 24.3 and 23.0, 12 of 2^19 54.1 and 51.3 and
-// 65.2 and 62.5, 12 SiLU of 6 * 2^20 153 and 147.  y is stored nt as well as through
-// (its forward with through alone: 71.3 and 88.5 us on the two passes above),
-// a short gradient is not (4.97 against 5.08 us at 2^22).
+// 65.2 and 62.5, 12 SiLU of 6 * 2^20 153 and 147.
+//
+// y is stored nt as well as through (the passes of 51.4M and 2^25 with y through
+// alone: 71.3 and 88.5 us), a short gradient is not (4.97 against 5.08 us at
+// 2^22).
 constexpr int64_t kNtFrom = int64_t{1} << 20, kNtUpto = int64_t{1} << 24;
 bool store_nt(int64_t bytes) { return bytes >= kNtFrom && bytes < kNtUpto; }
 

@@ -109,3 +109,15 @@ def test_a_ragged_stack_takes_no_longer_than_a_whole_one(act, bits, dt):
     a, b = min(t[0] for t in times), min(t[1] for t in times)
     print(f"[small] {act} {dt} whole {a:.1f} us, ragged {b:.1f} us", flush=True)
     assert b < 1.25 * a
+
+
+def test_sizes_no_memory_holds_are_refused():
+    # nothing is launched: the size is refused on the host
+    table = P.fit_table("gelu", 3, P.Weight(P.W_NORMAL, -10.0, 10.0), 1000).with_flags(P.FLAG_ELEMENT_FWD)
+    b = torch.zeros(4096, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    for n in (1 << 38, 1 << 62):
+        for dt in (P.F32, P.F16, P.BF16):
+            for f in (P.fwd_raw, P.bwd_raw):
+                assert f(table, dt, b.data_ptr(), b.data_ptr(), b.data_ptr(), n, stream) == -8
+    torch.cuda.synchronize()
